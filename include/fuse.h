@@ -205,7 +205,7 @@ int fuse_magg_noalloc(const fuse_expr *exprs, int k, const fuse_dense *X, const 
  * matrix X is the "sparse driver" that makes the whole operator sparse-safe).
  * The body is evaluated at the stored cells of the CSR matrix X only, with the
  * side inputs read at the same positions (dense sides by address, FUSE_SIDE_SPARSE
- * sides by a search in the side's row: 0 where the side stores nothing); it must be sparse-safe, i.e. be
+ * sides at the side's stored cell, 0 where the side stores nothing); it must be sparse-safe, i.e. be
  * zero wherever X has no stored cell (products with X, zero-preserving unaries,
  * sums of such), otherwise FUSE_EDESC.
  *   fuse_cell_csr: agg NONE -> nnz values on X's pattern; ROW -> rows(X) sums;

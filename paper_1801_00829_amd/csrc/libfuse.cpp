@@ -943,26 +943,58 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
             C = 4, G = 64;
     }
     const int RS = std::max(1, env_int("FUSE_CSR_RS", 1));
-    const int BLOCK = std::max(64, env_int("FUSE_CSR_BLOCK", 1024));
+    int BLOCK = std::max(64, env_int("FUSE_CSR_BLOCK", 1024));
+    const double mean_len = m > 0 ? (double)X->nnz / (double)m : 0.0;
+
+    const int SC = 4;                                    // cells per lane of the streaming skeleton (8: slower, 442 us on config 4)
+    const int stream_mode = env_int("FUSE_CSR_STREAM", 2);
+
+    // Sparse side inputs: the streaming skeleton with the bit set over the keys of a batch's rows (FUSE_CSR_XTAB: 0
+    // never, 1 by this rule).  At most three such sides (their cells travel in registers); as many rows per batch
+    // as its T slots hold at the mean row length, while their keys fit 1024 words (8 KB per wave).  12 waves per block
+    // (168 registers each).  Against the lane groups' bisection in LDS: 1e6 x 1000, a tenth stored in three matrices
+    // 1134 -> 662 us (8 waves 757 us; non-temporal loads 770 us); 597717 x 353, 30 cells per row, log-normal lengths
+    // 1092 -> 168 us; 139891 x 122, 5.5 per row 80 -> 21 us; 74111 x 1083, 190 per row 187 -> 114 us.  Where fewer than 16
+    // cells meet in a batch (few cells in wide rows) its fixed cost is not shared and the other forms stay.
+    int nsparse = 0;
+    for (int k = 0; k < nsides; ++k)
+        nsparse += prog.side_used[k] && sides[k].kind == FUSE_SIDE_SPARSE;
+    int tabr = 0, words = 0;
+    bool srp64 = false;
+    for (int k = 0; k < nsides; ++k)
+        srp64 |= prog.side_used[k] && sides[k].kind == FUSE_SIDE_SPARSE && sides[k].sp && sides[k].sp->rowptr_is64;
+    if (nsparse >= 1 && nsparse <= 3 && kd == 0 && n >= 1 && n <= 32 * 1024 && stream_mode != 0 && env_int("FUSE_CSR_XTAB", 1) != 0) {
+        const double fit = mean_len > 0.0 ? 64.0 * SC / mean_len : 63.0;
+        tabr = (int)std::min<double>(63.0, std::max(1.0, std::ceil(1.25 * fit)));
+        tabr = (int)std::min<int64_t>(tabr, 32 * 1024 / n);
+        words = (int)((tabr * n + 31) / 32);
+        words = words <= 64 ? 64 : (words + 127) / 128 * 128;          // per lane one word, or pairs
+        if (env_int("FUSE_CSR_XTAB", 1) == 1 && tabr * mean_len < 16.0) {
+            tabr = 0;
+        } else {
+            const int64_t wave_bytes = (64 * SC + 4) * 4 + std::max(prog.nred, 1) * 65 * 8 + words * 8 + nsparse * 64 * SC * 8;
+            BLOCK = env_int("FUSE_CSR_XTAB_BLOCK", 768);
+            BLOCK = (int)std::max<int64_t>(64, std::min<int64_t>(BLOCK, 120 * 1024 / wave_bytes * 64));
+        }
+    }
+    const bool xtab = tabr > 0;
     // Very short rows (a mean of up to 5.5 cells): the streaming skeleton, where a wave reads runs of
     // whole rows as contiguous cells.  Measured on 1000 columns, t(X)(Xv), 1e8 stored cells: 3 per row
     // 285 us against 500 us for lane groups, 10 per row 264 against 234; 5e7 stored cells: 4 per row
     // 135 against 157, 5 per row 132 against 144, 6 per row 126 against 119, 8 per row 124 against 115.
     // FUSE_CSR_STREAM: 0 never, 1 always, 2 by this rule.
-    const int stream_mode = env_int("FUSE_CSR_STREAM", 2);
-    const int SC = 4;                                    // cells per lane of the streaming skeleton (8: slower, 442 us on config 4)
     // bodies that never look at the row (no row aggregate, no per-row side, one value per cell)
     // run the streaming skeleton's flat form over the cell arrays, whatever the row lengths
     bool need_rid = prog.nred > 0 || ac == 2 || !prog.result_vec;
     for (int k = 0; k < nsides; ++k)
         need_rid |= prog.side_used[k] && (sides[k].kind == FUSE_SIDE_MATRIX || sides[k].kind == FUSE_SIDE_SPARSE || sides[k].kind == FUSE_SIDE_COLVEC);
     // (bodies with k-vectors run in the lane-group form only)
-    const double mean_len = m > 0 ? (double)X->nnz / (double)m : 0.0;
     // LDS the streaming form needs per block beside column sums and staged row vectors: a histogram of
     // 64 * SC + 4 counters and 65 row totals per row aggregate, per wave
-    const int64_t stream_fixed = (int64_t)(BLOCK / 64) * ((64 * SC + 4) * 4 + (int64_t)std::max(prog.nred, 1) * 65 * 8) + 2048;
-    const bool streaming = kd == 0 && stream_fixed <= 120 * 1024 &&
-                           (stream_mode == 1 || (stream_mode == 2 && (mean_len <= 5.5 || !need_rid)));
+    const int64_t stream_fixed = (int64_t)(BLOCK / 64) * ((64 * SC + 4) * 4 + (int64_t)std::max(prog.nred, 1) * 65 * 8 +
+                                                              (xtab ? words * 8 + nsparse * 64 * SC * 8 : 0)) + 2048;
+    const bool streaming = kd == 0 && (xtab || stream_fixed <= 120 * 1024) &&
+                           (xtab || stream_mode == 1 || (stream_mode == 2 && (mean_len <= 5.5 || !need_rid)));
 
     // LDS plan: the column accumulator first, then staged row-vector sides if they fit
     int nrv = 0;
@@ -982,14 +1014,12 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
     // Sparse side inputs in the lane-group form: every group stages the column indices of the side's row in LDS
     // (FUSE_SCAP entries per group and side: 1.5 x the side's mean row length, a power of two, while it fits
     // beside the column sums and the staged row vectors); longer rows of a side are searched in memory.
-    int nsparse = 0, scap = 0;
+    int scap = 0;
     if (!streaming) {
         double longest = 0.0;
         for (int k = 0; k < nsides; ++k)
-            if (prog.side_used[k] && sides[k].kind == FUSE_SIDE_SPARSE && sides[k].sp) {
-                ++nsparse;
+            if (prog.side_used[k] && sides[k].kind == FUSE_SIDE_SPARSE && sides[k].sp)
                 longest = std::max(longest, m > 0 ? (double)sides[k].sp->nnz / (double)m : 0.0);
-            }
         if (nsparse > 0 && env_int("FUSE_CSR_SCAP", -1) != 0) {
             scap = std::min(1024, std::max(G, next_pow2((int64_t)(1.5 * longest + 8.0))));
             if (env_int("FUSE_CSR_SCAP", -1) > 0)
@@ -1002,7 +1032,7 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
         }
     }
 
-    const int nt = env_int("FUSE_CSR_NT", streaming ? 1 : 0);
+    const int nt = env_int("FUSE_CSR_NT", streaming && !xtab ? 1 : 0);
     // lane-group form: the rows are dealt to the blocks in pieces of FUSE_CSR_ILV steps of a block (default 1:
     // 256 rows with 16 rows per wave and 16 waves), round-robin, when every block gets at least four pieces;
     // otherwise (and with FUSE_CSR_ILV=0) every block takes one contiguous range balanced by rows + stored cells.
@@ -1024,7 +1054,7 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
                                                             : "|g" + std::to_string(G) + "c" + std::to_string(C) + "r" + std::to_string(RS)) + "b" +
                             std::to_string(BLOCK) + "p" + std::to_string(npad) + "a" + std::to_string(naccpad) + "s" + std::to_string(stage_rv) + (cols_global ? "G" : "") +
                             "w" + std::to_string(X->rowptr_is64 != 0) + std::to_string(m < (1LL << 30)) + "nt" +
-                            std::to_string(nt) + "i" + std::to_string(ilv) + (scap ? "sp" + std::to_string(nsparse) + "x" + std::to_string(scap) : "");
+                            std::to_string(nt) + "i" + std::to_string(ilv) + (xtab ? "xt" + std::to_string(nsparse) + "r" + std::to_string(tabr) + "w" + std::to_string(words) : "") + (scap ? "sp" + std::to_string(nsparse) + "x" + std::to_string(scap) : "");
     std::shared_ptr<Plan> plan;
     int rc = rt.plan(key, name_prefix, [&](const std::string &name) {
         std::string s = kSrcArgs;
@@ -1042,7 +1072,9 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
              std::to_string(m < (1LL << 30)) + "\n#define FUSE_NPAD " +
              std::to_string(npad) + "\n#define FUSE_NACCPAD " + std::to_string(naccpad) + "\n#define FUSE_STAGE_RV " + std::to_string(stage_rv) +
              "\n#define FUSE_NRV " + std::to_string(std::max(nrv, 1)) + "\n#define FUSE_NSPARSE " + std::to_string(std::max(nsparse, 1)) +
-             "\n#define FUSE_SCAP " + std::to_string(scap) + "\n";
+             "\n#define FUSE_SCAP " + std::to_string(scap) + "\n#define FUSE_XTAB " + std::to_string(xtab) +
+             "\n#define FUSE_TABR " + std::to_string(tabr) + "\n#define FUSE_WORDS " + std::to_string(words) +
+             "\n#define FUSE_SRP64 " + std::to_string(srp64) + "\n";
         s += side_tables(sides, nsides, prog.side_used);
         s += emit_row_body(prog);
         s += streaming ? kSrcRowCsrStream : kSrcRowCsr;

@@ -978,6 +978,50 @@ def test_sparse_side_lookup_paths_agree(scap, monkeypatch):
     assert ("#define FUSE_SCAP %s\n" % scap) in F.last_source()
 
 
+def _csr_of_lengths(m, n, lens, seed):
+    """CSR with the given row lengths, ascending distinct columns, values in (0, 1]."""
+    rng = np.random.default_rng(seed)
+    ci = np.concatenate([np.sort(rng.choice(n, k, replace=False)) for k in lens] + [np.zeros(0, np.int64)]).astype(np.int32)
+    return np.concatenate([[0], np.cumsum(lens)]).astype(np.int64), ci, 1.0 - rng.random(int(np.sum(lens)))
+
+
+@pytest.mark.parametrize("m,n,mean,nsparse", [(200, 37, 3.0, 2), (5, 64, 64.0, 1), (97, 513, 255.5, 3), (60, 1000, 300.0, 2),
+                                              (33, 1025, 20.0, 1), (9, 32768, 700.0, 2)])
+def test_sparse_sides_streamed_with_the_rows(m, n, mean, nsparse):
+    """Sparse sides streamed beside X: batches of many short rows, rows at and beyond the 256 cells of a batch, key ranges
+    of one, two and 1024 words per row, sides with longer, shorter and empty rows, 32- and 64-bit offsets."""
+    import paper_1801_00829_amd as F
+    rng = np.random.default_rng(m + n)
+    mats = []
+    for q in range(nsparse + 1):
+        lens = np.minimum(n, np.round(mean * np.exp(0.8 * rng.standard_normal(m)))).astype(np.int64)
+        lens[rng.random(m) < 0.2] = 0
+        lens[:2] = min(n, 256 + q), min(n, 257)
+        mats.append(_csr_of_lengths(m, n, lens, 7 * q + n))
+    x = ops.make_csr(*mats[0], (m, n))
+    dense = [("matrix", ops.csr_to_dense(ops.make_csr(*s_, (m, n)))) for s_ in mats[1:]]
+    sd = dev_sides([("sparse", (*s_, (m, n), bool(q % 2))) for q, s_ in enumerate(mats[1:])])
+    expr = [("main",), ("side", 0), ("mul",)]
+    for q in range(1, nsparse):
+        expr += [("main",), ("side", q), ("mul",), ("add",)]
+    xd = dev_csr(*mats[0], (m, n), rowptr64=m % 2 == 1)
+    for agg in ("none", "row", "col", "full"):
+        ref = unfused.cell_csr(expr, x, dense, agg)
+        got = host(F.fuse_cell_csr(expr, xd, sd, agg))
+        # positive values: sums in another order differ by at most their length times the rounding of one addition
+        np.testing.assert_allclose(got, ref, rtol={"none": 1e-15, "full": 2.3e-16 * m * n}.get(agg, 2.3e-16 * max(m, n, 64)), atol=0)
+    assert "#define FUSE_XTAB 1" in F.last_source()
+    # a Row body with a row aggregate over the same cells
+    got = host(F.fuse_row(expr + [("main",), ("side", 0), ("mul",), ("rowsum",), ("mul",)], xd, sd, "none"))
+    ref = unfused.row_csr(expr + [("main",), ("side", 0), ("mul",), ("rowsum",), ("mul",)], x, dense, "none")
+    np.testing.assert_allclose(got, ref, rtol=2.3e-16 * max(n, 64), atol=0)
+    # the cells of a row in descending order are looked up one by one
+    rp, ci, va = mats[0]
+    order = np.concatenate([np.arange(rp[r], rp[r + 1])[::-1] for r in range(m)])
+    got = host(F.fuse_cell_csr(expr, dev_csr(rp, ci[order], va[order], (m, n)), sd, "none"))
+    np.testing.assert_allclose(got, unfused.cell_csr(expr, x, dense, "none")[order], rtol=1e-15, atol=0)
+
+
 # ------------------------------------------- Row with a matrix right-hand side ---
 
 MLOG_Q = [("side", 1), ("main",), ("side", 0), ("matmult",), ("mul",)]                   # Q = P * (X V)
