@@ -40,6 +40,9 @@ const char *kSrcRowMfma =
 const char *kSrcRowMfmaWave =
 #include "skel_row_mfma_wave.inc"
     ;
+const char *kSrcRowMfmaPipe =
+#include "skel_row_mfma_pipe.inc"
+    ;
 const char *kSrcRowCsr =
 #include "skel_row_csr.inc"
     ;
@@ -454,14 +457,47 @@ int row_mfma_impl(const Program &prog, const std::string &pkey, const fuse_dense
     int NWAVE = env_int("FUSE_MFMA_WAVES", 8);
     if (NWAVE != 4 && NWAVE != 8 && NWAVE != 16)
         NWAVE = 8;
-    const int ns_ = std::max(nsides, 1);
-    auto lds_bytes = [&](int nw) { return (16 * np + (int64_t)(nw + 2 + ns_) * 272 + (int64_t)ns_ * 16) * 8; };
+    auto lds_bytes = [&](int nw) {
+        const int ns = std::max(nsides, 1);
+        return (16 * np + (int64_t)(nw + 2 + ns) * 272 + (int64_t)ns * 16) * 8;
+    };
     while (NWAVE > 4 && lds_bytes(NWAVE) > 158 * 1024)
         NWAVE >>= 1;
     if (lds_bytes(NWAVE) > 158 * 1024)
         return fail(FUSE_EUNSUPPORTED, "internal: matrix-unit Row form chosen for a row tile that does not fit in LDS");
-    const int BLOCK = 64 * NWAVE;
-    const int64_t nld = (nvec + BLOCK / 16 - 1) / (BLOCK / 16);
+    // CSR input: cells per thread that travel in registers (the mean row length and a third, over the threads of a row)
+    const int csrx = Xs != nullptr;
+    const int rp64 = Xs && Xs->rowptr_is64;
+    auto csr_cap = [&](int threads) {
+        const double avg = m > 0 ? (double)Xs->nnz / (double)m : 1.0;
+        return (int)std::min<int64_t>(16, std::max<int64_t>(1, (int64_t)(avg * 1.34 / threads) + 1));
+    };
+    // Pipelined form (FUSE_MFMA_PIPE=0: never): 7 product waves and one for the generated code, one block per CU; the most
+    // rows per tile of which four tiles fit in LDS, while V, the running sums and two travelling tiles leave a thread 60 of
+    // its 256 registers.  2.4 GB, logistic regression core, block form / pipelined: n = 128 k = 4 586 / 564, k = 16
+    // 1285 / 1015 us; n = 256 460 / 466, 818 / 814; n = 500 540 / 438, 718 / 674; n = 784 494 / 436, 832 / 660; n = 1000
+    // 492 / 429, 1542 / 665.  CSR rows are scattered by as many waves as a tile has rows, so a tile of 4 gains nothing (784
+    // columns, a quarter stored, k = 10: 1472 / 1490 us) and few columns are cheaper in the block form (112 columns, 30 %
+    // stored, k = 10: 887 / 1048; 300 columns, 20 %, k = 5 / 10: 2033 / 1395, 2070 / 1518; 500 columns, 16 %, k = 5 / 10 / 16:
+    // 1048 / 867, 1075 / 996, 1106 / 1150).
+    int TR = 16;
+    bool pipe = false;
+    const int ns_ = std::max(nsides, 1), mp = (kd + 3) / 4, NPROD = 7;
+    const int64_t np_pipe = nct * 16 + (40 - nct * 16 % 32) % 32;          // 8 modulo 32
+    if (env_int("FUSE_MFMA_PIPE", 1) != 0 && (!Xs || (Xs->nnz > 0 && n >= 256 && kd <= 12))) {
+        for (int tr = Xs ? 8 : 16; tr >= (Xs ? 8 : 4) && !pipe; tr >>= 1) {
+            const int64_t lds = (4 * tr * np_pipe + (int64_t)(2 * NPROD + 3 + ns_) * tr * (4 * mp + 1)) * 8;
+            const int64_t held = (nct + NPROD - 1) / NPROD * mp * 4;
+            const int64_t travel = Xs ? (tr + NPROD - 1) / NPROD * (3 * csr_cap(64) + 4) : (nvec + 64 * NPROD / tr - 1) / (64 * NPROD / tr) * VEC * 2;
+            if (lds <= 158 * 1024 && held + 2 * travel <= 196) {
+                pipe = true;
+                TR = tr;
+            }
+        }
+    }
+    const int BLOCK = pipe ? 64 * NPROD + 64 : 64 * NWAVE;
+    const int loaders = pipe ? 64 * NPROD : BLOCK;               // threads that bring the tile in
+    const int64_t nld = (nvec + loaders / TR - 1) / (loaders / TR);
     // 4x4x4 products up to 4 classes (less padding, a higher instruction rate; FUSE_MFMA_M4: 0 never, 1 always).
     // With more groups of 4 classes V's operands take one register pair per group and column step of the wave:
     // 1e6 x 784, k = 10 spilled (4.6 against 1.6 ms); 1e6 x 256, k = 8: 365 / 588 against 443 / 469 us
@@ -470,32 +506,26 @@ int row_mfma_impl(const Program &prog, const std::string &pkey, const fuse_dense
     int m4 = env_int("FUSE_MFMA_M4", -1);
     if (m4 != 0 && m4 != 1)
         m4 = kd <= 4 ? 1 : 0;
-    // CSR input: cells per thread that travel in registers (the mean row length and a third, over the threads of a row)
-    const int csrx = Xs != nullptr;
-    const int rp64 = Xs && Xs->rowptr_is64;
-    int cap = 1;
-    if (Xs) {
-        const double avg = m > 0 ? (double)Xs->nnz / (double)m : 1.0;
-        cap = (int)std::min<int64_t>(16, std::max<int64_t>(1, (int64_t)(avg * 1.34 / (BLOCK / 16)) + 1));
-    }
-    const std::string key = std::string("rowmfma|") + pkey + "|" + side_key(sides, nsides) + "|v" + std::to_string(VEC) +
-                            "n" + std::to_string(nct) + "w" + std::to_string(NWAVE) + "nt" + std::to_string(env_int("FUSE_NT", 1)) +
+    const int cap = !Xs ? 1 : csr_cap(pipe ? 64 : BLOCK / 16);
+    const std::string key = std::string(pipe ? "rowmfmap|" : "rowmfma|") + pkey + "|" + side_key(sides, nsides) + "|v" + std::to_string(VEC) +
+                            "n" + std::to_string(nct) + (pipe ? "r" + std::to_string(TR) + "l" + std::to_string(nld) : "w" + std::to_string(NWAVE)) + "nt" + std::to_string(env_int("FUSE_NT", 1)) +
                             "m" + std::to_string(m4) + (csrx ? "csr" + std::to_string(rp64) + "c" + std::to_string(cap) : "");
     std::shared_ptr<Plan> plan;
-    int rc = rt.plan(key, "fuse_row_mfma", [&](const std::string &name) {
+    int rc = rt.plan(key, pipe ? "fuse_row_mfma_pipe" : "fuse_row_mfma", [&](const std::string &name) {
         std::string s = kSrcArgs;
         s += "#define FUSE_NT " + std::to_string(env_int("FUSE_NT", 1)) + "\n";
         s += kSrcCommon;
         s += "#define FUSE_KERNEL_NAME " + name + "\n";
-        s += "#define FUSE_M4 " + std::to_string(m4) + "\n";
+        s += "#define FUSE_M4 " + std::to_string(m4) + "\n#define FUSE_TR " + std::to_string(TR) + "\n#define FUSE_RPW " +
+             std::to_string((TR + NPROD - 1) / NPROD) + "\n";
         s += "#define FUSE_CSRX " + std::to_string(csrx) + "\n#define FUSE_RP64 " + std::to_string(rp64) + "\n#define FUSE_CAP " +
              std::to_string(cap) + "\n";
-        s += "#define FUSE_NWAVE " + std::to_string(NWAVE) + "\n#define FUSE_VEC " + std::to_string(VEC) + "\n#define FUSE_NP " + std::to_string(np) +
+        s += "#define FUSE_NWAVE " + std::to_string(pipe ? NPROD : NWAVE) + "\n#define FUSE_VEC " + std::to_string(VEC) + "\n#define FUSE_NP " + std::to_string(pipe ? np_pipe : np) +
              "\n#define FUSE_NCT " + std::to_string(nct) + "\n#define FUSE_NLD " + std::to_string(nld) +
              "\n#define FUSE_VSIDE " + std::to_string(vside) + "\n";
         s += side_tables(sides, nsides, prog.side_used);
         s += emit_row_body(prog);
-        s += kSrcRowMfma;
+        s += pipe ? kSrcRowMfmaPipe : kSrcRowMfma;
         g_last_source = s;
         return s;
     }, plan, g_err);
@@ -509,11 +539,11 @@ int row_mfma_impl(const Program &prog, const std::string &pkey, const fuse_dense
         return rc;
     if (m == 0 || n == 0)
         return zero_fill(fn, out, n * kd, stream);
-    const int64_t ntiles = (m + 15) / 16;
+    const int64_t ntiles = (m + TR - 1) / TR;
     // as many blocks per CU as their tiles fit in LDS (and the register file: 512 / waves-per-SIMD): the phases
     // of one block (tile store, Q, body, H) then overlap with another block's
     const int64_t by_lds = std::max<int64_t>(1, (158 * 1024) / lds_bytes(NWAVE));
-    const int64_t bpc = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(by_lds, 16 / NWAVE),
+    const int64_t bpc = pipe ? 1 : std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(by_lds, 16 / NWAVE),
                                                             env_int("FUSE_MFMA_BLOCKS_PER_CU", 4)));
     const int64_t gx = std::max<int64_t>(1, std::min<int64_t>(ntiles, (int64_t)rt.num_cus() * bpc));
     Workspace ws;
@@ -579,10 +609,13 @@ int row_dense_impl(const Program &prog, const std::string &pkey, const fuse_dens
         //  n = 64 k = 2 479 / 517 against 474 / 490, n = 32 k = 2 480 / 513 against 500 / 531, n = 100 k = 1
         //  462 / 470 against 481 / 490; block form: n = 256 k = 3 615 / 661 against 516 / 511 and n = 784 k = 3
         //  742 / 736 against 597 / 622, but n = 128 k = 3 570 / 644 against 659 / 734, n = 500 k = 4 630 / 672
-        //  against 676 / 723, n = 1000 k = 3 516 / 547 against 594 / 609: the rule for the block form stays at 4)
+        //  against 676 / 723, n = 1000 k = 3 516 / 547 against 594 / 609: the rule for the block form stays at 4);
+        //  pipelined form (rows of 120 columns and more), 2.4 GB, logistic regression core, vector form against it: k = 3
+        //  n = 128 568 / 544, 256 575 / 447, 500 509 / 434, 784 593 / 438, 1000 464 / 418, 1101 608 / 438; k = 2 n = 128
+        //  397 / 542, 256 410 / 443, 500 437 / 429, 784 428 / 431, 1000 384 / 416
         int min_k = env_int("FUSE_MFMA_MIN_K", -1);
         if (min_k < 0)
-            min_k = !mfma_wave_form(X, launch) ? 4 : n >= 48 ? 2 : n > 16 ? 3 : 4;
+            min_k = !mfma_wave_form(X, launch) ? (n >= 120 ? 3 : 4) : n >= 48 ? 2 : n > 16 ? 3 : 4;
         const int64_t tile_bytes = (16 * ((n + 15) / 16 * 16 + 1) + (int64_t)(4 + 2 + std::max(nsides, 1)) * 272 + 128) * 8;
         if (ac == 3 && min_k > 0 && kd >= min_k && n >= 16 && tile_bytes <= 158 * 1024 &&
             mfma_pattern(prog, sides, nsides, vside))

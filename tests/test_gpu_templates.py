@@ -1080,6 +1080,36 @@ def test_row_matrix_rhs_chain_and_mlogreg_core(shape, rhs_form):
                  scale=(absx @ absv).sum(1).max(), what="rowSums(Q)")
 
 
+@pytest.mark.parametrize("sparse", [False, True])
+@pytest.mark.parametrize("shape", [(1, 128, 4), (17, 120, 3), (4099, 161, 5), (8200, 300, 12), (3001, 500, 16), (2055, 541, 10),
+                                   (1027, 784, 10), (5, 1001, 8), (2049, 1051, 3)])
+def test_row_matrix_rhs_pipelined(shape, sparse):
+    """The pipelined matrix-unit form: last tiles and blocks with fewer tiles than the pipeline is long, column tiles dealt
+    unevenly, padded classes, odd columns and strided rows, per-row scalars, k-vectors and a constant side at once.
+    The bound: two sums of n and m products, at most (n + m + 8) * 2^-53 of the same sums of absolute values."""
+    import paper_1801_00829_amd as F
+    m, n, k = shape
+    rng = np.random.default_rng(5)
+    x, v, p, c = rng.normal(size=(m, n)), rng.normal(size=(n, k)), rng.uniform(size=(m, k)), rng.uniform(size=m)
+    expr = [("main",), ("main",), ("side", 0), ("matmult",), ("side", 1), ("mul",), ("side", 2), ("mul",), ("side", 3),
+            ("mul",), ("outerk",)]
+    sides = [("rhs", v), ("kvec", p), ("colvec", c), ("scalar", 0.5)]
+    if sparse:
+        x[rng.uniform(size=x.shape) > 0.3] = 0.0
+        x[0] = np.where(x[0] == 0.0, 1.0, x[0])                # a full row among short ones
+        rows, cols = np.nonzero(x)
+        rp = np.concatenate([[0], np.cumsum(np.bincount(rows, minlength=m))])
+        xd = dev_csr(rp, cols, x[rows, cols], (m, n), rowptr64=bool(k & 1))
+    else:
+        xd = to_dev(np.hstack([x, np.full((m, 3), np.nan)]))[:, :n] if k % 2 else to_dev(x)
+    print("pipelined", shape, sparse, flush=True)
+    got = host(F.fuse_row(expr, xd, dev_sides(sides), "col_t")).reshape(n, k)
+    assert F.last_kernel().startswith("fuse_row_mfma_pipe_") == (not sparse or (256 <= n <= 544 and 5 <= k <= 12))
+    ref = x.T @ (0.5 * c[:, None] * p * (x @ v))
+    scale = np.abs(x).T @ (0.5 * c[:, None] * p * (np.abs(x) @ np.abs(v)))
+    assert (np.abs(got - ref) <= 4 * (n + m + 8) * 2.0 ** -53 * scale + 1e-300).all()
+
+
 @pytest.mark.parametrize("k", [1, 3, 10, 16])
 def test_row_csr_matrix_rhs_on_all_patterns(k):
     """t(X)(XV), the MLogreg core and k-vector results over a CSR main input: products over the stored
