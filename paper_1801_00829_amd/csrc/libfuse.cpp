@@ -673,8 +673,11 @@ int row_dense_impl(const Program &prog, const std::string &pkey, const fuse_dens
         epl64 = 1;
     const int EPL = (int)epl64;
     int RS = env_int("FUSE_ROW_RS", 0);
+    // element-wise results hold no running sums per column: two wide rows in flight.  X * column vector * row vector to a
+    // matrix, one row / two: 99991 x 1001 366 / 320 us, 100000 x 1000 320 / 306
+    const bool map_only = ac == 0 && kd == 0 && prog.nstage == 0;
     if (RS <= 0)
-        RS = EPL >= 8 ? 1 : (EPL >= 3 ? 2 : 4);
+        RS = EPL >= 8 ? (map_only ? 2 : 1) : (EPL >= 3 ? 2 : 4);
     const int BLOCK = WPR > 1 ? std::max(128, 64 * WPR) : 256;
     if (WPR > 1 && BLOCK != 64 * WPR)
         WPR = BLOCK / 64;          // at least two waves per block
@@ -739,7 +742,9 @@ int row_dense_impl(const Program &prog, const std::string &pkey, const fuse_dens
     const int64_t rows_per_iter = WPR > 1 ? RS : (int64_t)(64 / G) * RS * NW;
     const int cus = rt.num_cus();
     int64_t gx = (m + rows_per_iter - 1) / rows_per_iter;
-    const int bpc = WPR > 1 ? std::max(1, 16 / WPR) : env_int("FUSE_ROW_BLOCKS_PER_CU", 2);
+    // element-wise results: three blocks per CU, 2 / 3 / 4 blocks: 99991 x 77 34 / 30.5 / 28 us, 260001 x 301 244 / 234 / 244,
+    // 99991 x 1001 320 / 322 / 327
+    const int bpc = WPR > 1 ? std::max(1, 16 / WPR) : env_int("FUSE_ROW_BLOCKS_PER_CU", map_only ? 3 : 2);
     const int64_t cap = std::max<int64_t>(1, (int64_t)cus * bpc / stripes);
     gx = std::min(gx, cap);
     Workspace ws;
