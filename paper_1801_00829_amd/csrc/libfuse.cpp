@@ -1006,7 +1006,7 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
         tabr = (int)std::min<double>(63.0, std::max(1.0, std::ceil(1.25 * fit)));
         tabr = (int)std::min<int64_t>(tabr, 32 * 1024 / n);
         words = (int)((tabr * n + 31) / 32);
-        words = words <= 64 ? 64 : (words + 127) / 128 * 128;          // per lane one word, or pairs
+        words = std::max(64, next_pow2(words));          // (so one operator has at most five plans of this form)
         if (env_int("FUSE_CSR_XTAB", 1) == 1 && tabr * mean_len < 16.0) {
             tabr = 0;
         } else {
@@ -1092,7 +1092,7 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
                                                             : "|g" + std::to_string(G) + "c" + std::to_string(C) + "r" + std::to_string(RS)) + "b" +
                             std::to_string(BLOCK) + "p" + std::to_string(npad) + "a" + std::to_string(naccpad) + "s" + std::to_string(stage_rv) + (cols_global ? "G" : "") +
                             "w" + std::to_string(X->rowptr_is64 != 0) + std::to_string(m < (1LL << 30)) + "nt" +
-                            std::to_string(nt) + "i" + std::to_string(ilv) + (xtab ? "xt" + std::to_string(nsparse) + "r" + std::to_string(tabr) + "w" + std::to_string(words) : "") + (scap ? "sp" + std::to_string(nsparse) + "x" + std::to_string(scap) : "");
+                            std::to_string(nt) + "i" + std::to_string(ilv) + (xtab ? "xt" + std::to_string(nsparse) + "w" + std::to_string(words) : "") + (scap ? "sp" + std::to_string(nsparse) + "x" + std::to_string(scap) : "");
     std::shared_ptr<Plan> plan;
     int rc = rt.plan(key, name_prefix, [&](const std::string &name) {
         std::string s = kSrcArgs;
@@ -1111,7 +1111,7 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
              std::to_string(npad) + "\n#define FUSE_NACCPAD " + std::to_string(naccpad) + "\n#define FUSE_STAGE_RV " + std::to_string(stage_rv) +
              "\n#define FUSE_NRV " + std::to_string(std::max(nrv, 1)) + "\n#define FUSE_NSPARSE " + std::to_string(std::max(nsparse, 1)) +
              "\n#define FUSE_SCAP " + std::to_string(scap) + "\n#define FUSE_XTAB " + std::to_string(xtab) +
-             "\n#define FUSE_TABR " + std::to_string(tabr) + "\n#define FUSE_WORDS " + std::to_string(words) +
+             "\n#define FUSE_WORDS " + std::to_string(words) +
              "\n#define FUSE_SRP64 " + std::to_string(srp64) + "\n";
         s += side_tables(sides, nsides, prog.side_used);
         s += emit_row_body(prog);

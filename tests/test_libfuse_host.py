@@ -213,6 +213,17 @@ def test_sparse_side_inputs_host_checks(F):
     assert lib.fuse_prepare_cell_csr(ctypes.byref(e_), ctypes.byref(xs), sides, 1, 1) == 0
 
 
+def test_sparse_side_plans_follow_the_sparsity_in_few_steps(F):
+    """An operator over sparse sides whose sparsity changes from step to step compiles a handful of plans: five sizes of
+    the streaming form's bit set, beside the powers of two of the other forms."""
+    seen, m, n = set(), 1000, 1000
+    for mean in range(2, 200, 3):
+        F.prepare_cell_csr(XYZ[:3], (m, n), mean * m, [("sparse", (0, None, mean * m, (m, n)))], "full")
+        if "#define FUSE_XTAB 1\n" in F.last_source():
+            seen.add(F.last_kernel())
+    assert 1 <= len(seen) <= 5, seen
+
+
 def test_row_type_checking_and_sparse_safety(F):
     dot_v = [("main",), ("side", 0), ("dot",)]
     F.prepare_row(dot_v, (100, 10), [("rowvec", None)], "none")            # scalar result, per row
