@@ -998,6 +998,7 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
     for (int k = 0; k < nsides; ++k)
         nsparse += prog.side_used[k] && sides[k].kind == FUSE_SIDE_SPARSE;
     int tabr = 0, words = 0;
+    auto tab_bytes = [](int w) { return (int64_t)w * 8 + (w >= 256 ? 64 * 16 : 0); };      // (the lanes' parts are padded)
     bool srp64 = false;
     for (int k = 0; k < nsides; ++k)
         srp64 |= prog.side_used[k] && sides[k].kind == FUSE_SIDE_SPARSE && sides[k].sp && sides[k].sp->rowptr_is64;
@@ -1010,7 +1011,7 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
         if (env_int("FUSE_CSR_XTAB", 1) == 1 && tabr * mean_len < 16.0) {
             tabr = 0;
         } else {
-            const int64_t wave_bytes = (64 * SC + 4) * 4 + std::max(prog.nred, 1) * 65 * 8 + words * 8 + nsparse * 64 * SC * 8;
+            const int64_t wave_bytes = (64 * SC + 4) * 4 + std::max(prog.nred, 1) * 65 * 8 + tab_bytes(words) + nsparse * 64 * SC * 8;
             BLOCK = env_int("FUSE_CSR_XTAB_BLOCK", 768);
             BLOCK = (int)std::max<int64_t>(64, std::min<int64_t>(BLOCK, 120 * 1024 / wave_bytes * 64));
         }
@@ -1030,7 +1031,7 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
     // LDS the streaming form needs per block beside column sums and staged row vectors: a histogram of
     // 64 * SC + 4 counters and 65 row totals per row aggregate, per wave
     const int64_t stream_fixed = (int64_t)(BLOCK / 64) * ((64 * SC + 4) * 4 + (int64_t)std::max(prog.nred, 1) * 65 * 8 +
-                                                              (xtab ? words * 8 + nsparse * 64 * SC * 8 : 0)) + 2048;
+                                                              (xtab ? tab_bytes(words) + nsparse * 64 * SC * 8 : 0)) + 2048;
     const bool streaming = kd == 0 && (xtab || stream_fixed <= 120 * 1024) &&
                            (xtab || stream_mode == 1 || (stream_mode == 2 && (mean_len <= 5.5 || !need_rid)));
 

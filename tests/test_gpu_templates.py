@@ -1022,6 +1022,34 @@ def test_sparse_sides_streamed_with_the_rows(m, n, mean, nsparse):
     np.testing.assert_allclose(got, unfused.cell_csr(expr, x, dense, "none")[order], rtol=1e-15, atol=0)
 
 
+@pytest.mark.parametrize("n,mean,words", [(30, 20.0, 64), (100, 13.0, 128), (300, 20.0, 256), (500, 18.0, 512), (1000, 12.0, 1024), (20011, 4.0, 1024)])
+def test_sparse_sides_streamed_bit_set_sizes(n, mean, words, monkeypatch):
+    """Every size of the streaming form's bit set (lanes with one, two and up to 16 words, their parts side by side or apart),
+    keys in the first and the last column, and batches in which X stores nothing beside full rows of the side."""
+    import paper_1801_00829_amd as F
+    monkeypatch.setenv("FUSE_CSR_XTAB", "2")
+    F.cache_clear()                                          # (the source is that of the last plan compiled)
+    m = 700
+    rng = np.random.default_rng(n)
+    xl = np.minimum(n, rng.poisson(mean, m))
+    yl = np.minimum(n, rng.poisson(mean, m))
+    xl[200:330] = 0
+    yl[200:330] = min(n, 300)
+    x, y = _csr_of_lengths(m, n, xl, 1), _csr_of_lengths(m, n, yl, 2)
+    for mat in (x, y):                                       # the first and the last column meet in many rows
+        rp, ci = mat[0], mat[1]
+        for r in range(0, m, 3):
+            if rp[r + 1] - rp[r] >= 2:
+                ci[rp[r]], ci[rp[r + 1] - 1] = 0, n - 1
+    xc = ops.make_csr(*x, (m, n))
+    expr = [("main",), ("side", 0), ("mul",)]
+    got = host(F.fuse_cell_csr(expr, dev_csr(*x, (m, n)), dev_sides([("sparse", (*y, (m, n)))]), "none"))
+    assert ("#define FUSE_WORDS %d\n" % words) in F.last_source()
+    np.testing.assert_allclose(got, unfused.cell_csr(expr, xc, [("matrix", ops.csr_to_dense(ops.make_csr(*y, (m, n))))], "none"),
+                               rtol=1e-15, atol=0)
+    assert np.count_nonzero(got) >= m // 8
+
+
 # ------------------------------------------- Row with a matrix right-hand side ---
 
 MLOG_Q = [("side", 1), ("main",), ("side", 0), ("matmult",), ("mul",)]                   # Q = P * (X V)
