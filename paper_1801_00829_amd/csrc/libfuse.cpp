@@ -989,8 +989,8 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
 
     // Sparse side inputs: the streaming skeleton with the bit set over the keys of a batch's rows (FUSE_CSR_XTAB: 0
     // never, 1 by this rule).  At most three such sides (their cells travel in registers); as many rows per batch
-    // as its T slots hold at the mean row length, while their keys fit 1024 words (8 KB per wave).  12 waves per block
-    // (168 registers each).  Against the lane groups' bisection in LDS: 1e6 x 1000, a tenth stored in three matrices
+    // as its T slots hold at the mean row length, while their keys fit 1024 words (8 KB per wave).
+    // Against the lane groups' bisection in LDS: 1e6 x 1000, a tenth stored in three matrices
     // 1134 -> 662 us (8 waves 757 us; non-temporal loads 770 us); 597717 x 353, 30 cells per row, log-normal lengths
     // 1092 -> 168 us; 139891 x 122, 5.5 per row 80 -> 21 us; 74111 x 1083, 190 per row 187 -> 114 us.  Where fewer than 16
     // cells meet in a batch (few cells in wide rows) its fixed cost is not shared and the other forms stay.
@@ -1012,8 +1012,14 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
             tabr = 0;
         } else {
             const int64_t wave_bytes = (64 * SC + 4) * 4 + std::max(prog.nred, 1) * 65 * 8 + tab_bytes(words) + nsparse * 64 * SC * 8;
-            BLOCK = env_int("FUSE_CSR_XTAB_BLOCK", 768);
-            BLOCK = (int)std::max<int64_t>(64, std::min<int64_t>(BLOCK, 120 * 1024 / wave_bytes * 64));
+            // 12 waves per block leave a lane 168 registers, and so do 9 to 11; 8 leave 256.  The cells of two sides on their way
+            // just fit in 168 (18 spilled), those of three don't (283 spilled): 8 waves for three sides and where LDS
+            // holds fewer than 12 waves of two.  2e7 cells of X and of each side, 12 (or what LDS holds) / 8 waves: three
+            // sides, 1000 columns, 100 per row 788 / 226 us, 20 per row 820 / 263; 122 columns, 20 per row 703 / 234; two
+            // sides, 1000 columns, 100 per row 158 / 170, 20 per row (11 waves) 232 / 195; 353 columns, 10 per row 229 / 193.
+            const int64_t waves = 120 * 1024 / wave_bytes;
+            BLOCK = env_int("FUSE_CSR_XTAB_BLOCK", nsparse == 3 || (nsparse == 2 && waves < 12) ? 512 : 768);
+            BLOCK = (int)std::max<int64_t>(64, std::min<int64_t>(BLOCK, waves * 64));
         }
     }
     const bool xtab = tabr > 0;

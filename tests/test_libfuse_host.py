@@ -224,6 +224,16 @@ def test_sparse_side_plans_follow_the_sparsity_in_few_steps(F):
     assert 1 <= len(seen) <= 5, seen
 
 
+def test_three_streamed_sides_run_with_the_registers_of_eight_waves(F):
+    """The cells of three sides on their way take more than the 168 registers per lane that blocks of more than 8 waves have."""
+    for mean, n in ((100, 1000), (20, 1000), (20, 122)):
+        m = 100000
+        F.cache_clear()
+        F.prepare_cell_csr(XYZ + [("side", 2), ("mul",)], (m, n), m * mean, [("sparse", (0, None, m * mean, (m, n)))] * 3, "full")
+        src = F.last_source()
+        assert "#define FUSE_XTAB 1\n" in src and int(re.search(r"#define FUSE_BLOCK (\d+)", src).group(1)) <= 512
+
+
 def test_row_type_checking_and_sparse_safety(F):
     dot_v = [("main",), ("side", 0), ("dot",)]
     F.prepare_row(dot_v, (100, 10), [("rowvec", None)], "none")            # scalar result, per row
