@@ -988,12 +988,19 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
     const int stream_mode = env_int("FUSE_CSR_STREAM", 2);
 
     // Sparse side inputs: the streaming skeleton with the bit set over the keys of a batch's rows (FUSE_CSR_XTAB: 0
-    // never, 1 by this rule).  At most three such sides (their cells travel in registers); as many rows per batch
-    // as its T slots hold at the mean row length, while their keys fit 1024 words (8 KB per wave).
-    // Against the lane groups' bisection in LDS: 1e6 x 1000, a tenth stored in three matrices
-    // 1134 -> 662 us (8 waves 757 us; non-temporal loads 770 us); 597717 x 353, 30 cells per row, log-normal lengths
-    // 1092 -> 168 us; 139891 x 122, 5.5 per row 80 -> 21 us; 74111 x 1083, 190 per row 187 -> 114 us.  Where fewer than 16
-    // cells meet in a batch (few cells in wide rows) its fixed cost is not shared and the other forms stay.
+    // never, 1 by this rule, 2 whenever it can run).  At most three such sides (their cells travel in registers); as many
+    // rows per batch as its T slots hold at the mean row length, while their keys fit 1024 words (8 KB per wave).  Against
+    // the lane groups' bisection in LDS: 1e6 x 1000, a tenth stored in three matrices 1134 -> 662 us (8 waves 757 us;
+    // non-temporal loads 770 us); 597717 x 353, 30 cells per row, log-normal lengths 1092 -> 168 us; 139891 x 122, 5.5 per
+    // row 80 -> 21 us; 74111 x 1083, 190 per row 187 -> 114 us.
+    // The rule compares what a batch costs with what its rows and cells cost in the other forms, in ps of the whole chip:
+    // a batch 460, 4 per 64 words and 420 per started 256 cells of a side (with 12 waves); a row 20, a cell of X 4, a cell of
+    // a side 1.6, 5.1 or 10 (one, two or three sides; up to 5.5 cells per row, where the other form is this skeleton with
+    // bisections, 1.6 and 5 per row and side), rows beyond 256 cells more by the square root of their length.
+    // Fitted to even row lengths over 122 - 30000 columns, 1 - 200 cells per row, sides of 0.3 - 8 times X's cells (within
+    // 20 %).  sum(X*Y), other form / this one, even and log-normal row lengths: 1000 columns, 20 cells per row in both 153 /
+    // 112 and 739 / 131 us, 2 and 16 per row 76 / 96 and 82 / 100, 10 and 80 47 / 64 and 248 / 75; 10000 columns, 50 and 50
+    // 127 / 199 and 642 / 254; 3000 columns, 1000 and 1000 424 / 119 and 614 / 169.
     int nsparse = 0;
     for (int k = 0; k < nsides; ++k)
         nsparse += prog.side_used[k] && sides[k].kind == FUSE_SIDE_SPARSE;
@@ -1002,25 +1009,38 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
     bool srp64 = false;
     for (int k = 0; k < nsides; ++k)
         srp64 |= prog.side_used[k] && sides[k].kind == FUSE_SIDE_SPARSE && sides[k].sp && sides[k].sp->rowptr_is64;
-    if (nsparse >= 1 && nsparse <= 3 && kd == 0 && n >= 1 && n <= 32 * 1024 && stream_mode != 0 && env_int("FUSE_CSR_XTAB", 1) != 0) {
-        const double fit = mean_len > 0.0 ? 64.0 * SC / mean_len : 63.0;
+    const int xtab_mode = env_int("FUSE_CSR_XTAB", 1);
+    if (nsparse >= 1 && nsparse <= 3 && kd == 0 && X->nnz > 0 && n <= 32 * 1024 && stream_mode != 0 && xtab_mode != 0) {
+        const double T = 64.0 * SC, fit = mean_len > 0.0 ? T / mean_len : 63.0;
         tabr = (int)std::min<double>(63.0, std::max(1.0, std::ceil(1.25 * fit)));
         tabr = (int)std::min<int64_t>(tabr, 32 * 1024 / n);
         words = (int)((tabr * n + 31) / 32);
         words = std::max(64, next_pow2(words));          // (so one operator has at most five plans of this form)
-        if (env_int("FUSE_CSR_XTAB", 1) == 1 && tabr * mean_len < 16.0) {
+        const int64_t wave_bytes = (64 * SC + 4) * 4 + std::max(prog.nred, 1) * 65 * 8 + tab_bytes(words) + nsparse * 64 * SC * 8;
+        // 12 waves per block leave a lane 168 registers, and so do 9 to 11; 8 leave 256.  The cells of two sides on their way
+        // just fit in 168 (18 spilled), those of three don't (283 spilled): 8 waves for three sides and where LDS
+        // holds fewer than 12 waves of two.  2e7 cells of X and of each side, 12 (or what LDS holds) / 8 waves: three
+        // sides, 1000 columns, 100 per row 788 / 226 us, 20 per row 820 / 263; 122 columns, 20 per row 703 / 234; two
+        // sides, 1000 columns, 100 per row 158 / 170, 20 per row (11 waves) 232 / 195; 353 columns, 10 per row 229 / 193.
+        const int64_t waves = 120 * 1024 / wave_bytes;
+        int block = env_int("FUSE_CSR_XTAB_BLOCK", nsparse == 3 || (nsparse == 2 && waves < 12) ? 512 : 768);
+        block = (int)std::max<int64_t>(64, std::min<int64_t>(block, waves * 64));
+        const double rows = mean_len > T ? 1.0 / std::ceil(mean_len / T)
+                                         : std::max(1.0, std::min(std::floor(fit), (double)std::min<int64_t>(63, words * 32 / n)));
+        const double cells = rows * mean_len;            // of a batch
+        double batch = 460.0 + 4.0 * words / 64, other = 20.0 * rows + 4.0 * cells;
+        for (int k = 0; k < nsides; ++k)
+            if (prog.side_used[k] && sides[k].kind == FUSE_SIDE_SPARSE) {
+                const double side = sides[k].sp && m > 0 ? rows * ((double)sides[k].sp->nnz / (double)m) : 0.0;
+                batch += 420.0 * std::max(1.0, side / T);
+                other += mean_len <= 5.5 ? 5.0 * rows + 1.6 * side : (nsparse == 1 ? 1.6 : nsparse == 2 ? 5.1 : 10.0) * side;
+            }
+        batch *= nsparse == 1 ? 768.0 / block : block >= 768 ? 1.0 : 1.1 * 512 / block;
+        other *= mean_len > T ? 1.5 * std::sqrt(mean_len / T) : 1.0;
+        if (xtab_mode == 1 && batch > other)
             tabr = 0;
-        } else {
-            const int64_t wave_bytes = (64 * SC + 4) * 4 + std::max(prog.nred, 1) * 65 * 8 + tab_bytes(words) + nsparse * 64 * SC * 8;
-            // 12 waves per block leave a lane 168 registers, and so do 9 to 11; 8 leave 256.  The cells of two sides on their way
-            // just fit in 168 (18 spilled), those of three don't (283 spilled): 8 waves for three sides and where LDS
-            // holds fewer than 12 waves of two.  2e7 cells of X and of each side, 12 (or what LDS holds) / 8 waves: three
-            // sides, 1000 columns, 100 per row 788 / 226 us, 20 per row 820 / 263; 122 columns, 20 per row 703 / 234; two
-            // sides, 1000 columns, 100 per row 158 / 170, 20 per row (11 waves) 232 / 195; 353 columns, 10 per row 229 / 193.
-            const int64_t waves = 120 * 1024 / wave_bytes;
-            BLOCK = env_int("FUSE_CSR_XTAB_BLOCK", nsparse == 3 || (nsparse == 2 && waves < 12) ? 512 : 768);
-            BLOCK = (int)std::max<int64_t>(64, std::min<int64_t>(BLOCK, waves * 64));
-        }
+        else
+            BLOCK = block;
     }
     const bool xtab = tabr > 0;
     // Very short rows (a mean of up to 5.5 cells): the streaming skeleton, where a wave reads runs of

@@ -234,6 +234,17 @@ def test_three_streamed_sides_run_with_the_registers_of_eight_waves(F):
         assert "#define FUSE_XTAB 1\n" in src and int(re.search(r"#define FUSE_BLOCK (\d+)", src).group(1)) <= 512
 
 
+@pytest.mark.parametrize("n,mean,side,nsides,streamed", [
+    (1000, 2, 500, 1, False), (1000, 1, 1, 1, False), (1000, 10, 80, 1, False), (10000, 10, 10, 2, False),       # bisection
+    (1000, 100, 100, 2, True), (1000, 10, 10, 1, True), (122, 5, 5, 1, True), (1000, 20, 60, 2, True), (3000, 1000, 1000, 1, True)])
+def test_sparse_sides_are_streamed_where_that_costs_less(F, n, mean, side, nsides, streamed):
+    """The choice between streaming the sides' cells and searching them takes both sides' cells into account."""
+    m = 200000
+    F.cache_clear()
+    F.prepare_cell_csr(XYZ if nsides == 2 else XYZ[:3], (m, n), m * mean, [("sparse", (0, None, m * side, (m, n)))] * nsides, "full")
+    assert ("#define FUSE_XTAB 1\n" in F.last_source()) == streamed
+
+
 def test_row_type_checking_and_sparse_safety(F):
     dot_v = [("main",), ("side", 0), ("dot",)]
     F.prepare_row(dot_v, (100, 10), [("rowvec", None)], "none")            # scalar result, per row
