@@ -995,8 +995,11 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
     // row 80 -> 21 us; 74111 x 1083, 190 per row 187 -> 114 us.
     // The rule compares what a batch costs with what its rows and cells cost in the other forms, in ps of the whole chip:
     // a batch 460, 4 per 64 words and 420 per started 256 cells of a side (with 12 waves); a row 20, a cell of X 4, a cell of
-    // a side 1.6, 5.1 or 10 (one, two or three sides; up to 5.5 cells per row, where the other form is this skeleton with
-    // bisections, 1.6 and 5 per row and side), rows beyond 256 cells more by the square root of their length.
+    // a side 1.6, 5.1 or 8 (one, two or three sides; up to 5.5 cells per row, where the other form is this skeleton with
+    // bisections, 1.6 and 5 per row and side, and three quarters of it all, since matrices that fit in the caches gain
+    // more there: 874 columns, 2.7 per row, 430826 rows 18 / 31 us), rows beyond 256 cells more by the square root of their
+    // length.  320 calls drawn over 60 - 30000 columns, one to three sides, even and log-normal rows: 0.64 of the other
+    // forms' time in the geometric mean, at most 1.4 times in a single one.
     // Fitted to even row lengths over 122 - 30000 columns, 1 - 200 cells per row, sides of 0.3 - 8 times X's cells (within
     // 20 %).  sum(X*Y), other form / this one, even and log-normal row lengths: 1000 columns, 20 cells per row in both 153 /
     // 112 and 739 / 131 us, 2 and 16 per row 76 / 96 and 82 / 100, 10 and 80 47 / 64 and 248 / 75; 10000 columns, 50 and 50
@@ -1033,10 +1036,10 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
             if (prog.side_used[k] && sides[k].kind == FUSE_SIDE_SPARSE) {
                 const double side = sides[k].sp && m > 0 ? rows * ((double)sides[k].sp->nnz / (double)m) : 0.0;
                 batch += 420.0 * std::max(1.0, side / T);
-                other += mean_len <= 5.5 ? 5.0 * rows + 1.6 * side : (nsparse == 1 ? 1.6 : nsparse == 2 ? 5.1 : 10.0) * side;
+                other += mean_len <= 5.5 ? 5.0 * rows + 1.6 * side : (nsparse == 1 ? 1.6 : nsparse == 2 ? 5.1 : 8.0) * side;
             }
-        batch *= nsparse == 1 ? 768.0 / block : block >= 768 ? 1.0 : 1.1 * 512 / block;
-        other *= mean_len > T ? 1.5 * std::sqrt(mean_len / T) : 1.0;
+        batch *= 768.0 / block;
+        other *= mean_len > T ? 1.5 * std::sqrt(mean_len / T) : mean_len <= 5.5 ? 0.75 : 1.0;
         if (xtab_mode == 1 && batch > other)
             tabr = 0;
         else
