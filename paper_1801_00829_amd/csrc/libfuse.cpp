@@ -1021,12 +1021,17 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
         words = std::max(64, next_pow2(words));          // (so one operator has at most five plans of this form)
         const int64_t wave_bytes = (64 * SC + 4) * 4 + std::max(prog.nred, 1) * 65 * 8 + tab_bytes(words) + nsparse * 64 * SC * 8;
         // 12 waves per block leave a lane 168 registers, and so do 9 to 11; 8 leave 256.  The cells of two sides on their way
-        // just fit in 168 (18 spilled), those of three don't (283 spilled): 8 waves for three sides and where LDS
-        // holds fewer than 12 waves of two.  2e7 cells of X and of each side, 12 (or what LDS holds) / 8 waves: three
-        // sides, 1000 columns, 100 per row 788 / 226 us, 20 per row 820 / 263; 122 columns, 20 per row 703 / 234; two
-        // sides, 1000 columns, 100 per row 158 / 170, 20 per row (11 waves) 232 / 195; 353 columns, 10 per row 229 / 193.
+        // just fit in 168 beside full and row aggregates with at most one aggregate per row (18 spilled), but not beside
+        // results per cell or column or a matrix side (73 - 129 spilled), and those of three sides never (283 spilled).
+        // 2e7 cells of X and of each side, 12 (or what LDS holds) / 8 waves: three sides, 1000 columns, 100 per row 788 /
+        // 226 us, 20 per row 820 / 263; 122 columns, 20 per row 703 / 234; two sides, 1000 columns, 100 per row 158 / 170,
+        // 20 per row (11 waves) 232 / 195, 353 columns, 10 per row 229 / 193; row sums 199 / 205, a row aggregate 222 / 244,
+        // two 296 / 258, column sums 298 / 180, results per cell 490 / 223 (bisection 280).
+        bool narrow = nsparse == 2 && (ac == 1 || ac == 2 || !prog.result_vec) && prog.nred <= 1;
+        for (int k = 0; k < nsides; ++k)
+            narrow = narrow && !(prog.side_used[k] && sides[k].kind == FUSE_SIDE_MATRIX);
         const int64_t waves = 120 * 1024 / wave_bytes;
-        int block = env_int("FUSE_CSR_XTAB_BLOCK", nsparse == 3 || (nsparse == 2 && waves < 12) ? 512 : 768);
+        int block = env_int("FUSE_CSR_XTAB_BLOCK", nsparse == 1 || (narrow && waves >= 12) ? 768 : 512);
         block = (int)std::max<int64_t>(64, std::min<int64_t>(block, waves * 64));
         const double rows = mean_len > T ? 1.0 / std::ceil(mean_len / T)
                                          : std::max(1.0, std::min(std::floor(fit), (double)std::min<int64_t>(63, words * 32 / n)));

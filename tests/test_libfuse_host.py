@@ -224,6 +224,16 @@ def test_sparse_side_plans_follow_the_sparsity_in_few_steps(F):
     assert 1 <= len(seen) <= 5, seen
 
 
+@pytest.mark.parametrize("agg", ["none", "col"])
+def test_two_streamed_sides_with_stored_results_run_with_the_registers_of_eight_waves(F, agg):
+    """Results per cell or per column beside two sides on their way take more registers than 12 waves leave."""
+    m, n, nnz = 100000, 1000, 10000000
+    F.cache_clear()
+    F.prepare_cell_csr(XYZ, (m, n), nnz, [("sparse", (0, None, nnz, (m, n)))] * 2, agg)
+    src = F.last_source()
+    assert "#define FUSE_XTAB 1\n" in src and int(re.search(r"#define FUSE_BLOCK (\d+)", src).group(1)) <= 512
+
+
 def test_three_streamed_sides_run_with_the_registers_of_eight_waves(F):
     """The cells of three sides on their way take more than the 168 registers per lane that blocks of more than 8 waves have."""
     for mean, n in ((100, 1000), (20, 1000), (20, 122)):
