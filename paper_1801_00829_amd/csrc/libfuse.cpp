@@ -987,6 +987,17 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
     const int SC = 4;                                    // cells per lane of the streaming skeleton (8: slower, 442 us on config 4)
     const int stream_mode = env_int("FUSE_CSR_STREAM", 2);
 
+    // LDS plan: the column accumulator first (2), then staged row-vector sides (1) if they fit into the budget
+    int nrv = 0;
+    for (int k = 0; k < nsides; ++k)
+        nrv += prog.side_used[k] && sides[k].kind == FUSE_SIDE_ROWVEC;
+    const bool col_acc = ac == 3 && rk != KIND_K;          // per-column running sums (k per column for OUTERK)
+    auto in_lds = [&](int64_t budget) {
+        const bool cols = col_acc && n * nacck * 8 <= budget - 4096;
+        const bool rv = nrv > 0 && ((cols ? n * nacck : 0) + (int64_t)nrv * n) * 8 <= budget - 1024;
+        return (cols ? 2 : 0) + (rv ? 1 : 0);
+    };
+
     // Sparse side inputs: the streaming skeleton with the bit set over the keys of a batch's rows (FUSE_CSR_XTAB: 0
     // never, 1 by this rule, 2 whenever it can run).  At most three such sides (their cells travel in registers); as many
     // rows per batch as its T slots hold at the mean row length, while their keys fit 1024 words (8 KB per wave).  Against
@@ -1045,7 +1056,12 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
             }
         batch *= 768.0 / block;
         other *= mean_len > T ? 1.5 * std::sqrt(mean_len / T) : mean_len <= 5.5 ? 0.75 : 1.0;
-        if (xtab_mode == 1 && batch > other)
+        // Column sums and row vectors that the other form keeps in LDS stay there.  3e7 cells in X and one side, 150 per
+        // row, column sums in LDS beside the search / as atomics on memory beside the bit sets: 8000 columns 277 / 1322 us,
+        // 12000 273 / 1747; a row vector, 6000 columns 259 / 308, 12000 244 / 315.
+        const int64_t fixed = (int64_t)(block / 64) * wave_bytes + 2048;
+        const int lost = in_lds(mean_len <= 5.5 ? 96 * 1024 : 144 * 1024) & ~in_lds(std::min<int64_t>(96 * 1024, 156 * 1024 - fixed));
+        if (xtab_mode == 1 && (batch > other || lost))
             tabr = 0;
         else
             BLOCK = block;
@@ -1069,18 +1085,13 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
     const bool streaming = kd == 0 && (xtab || stream_fixed <= 120 * 1024) &&
                            (xtab || stream_mode == 1 || (stream_mode == 2 && (mean_len <= 5.5 || !need_rid)));
 
-    // LDS plan: the column accumulator first, then staged row-vector sides if they fit
-    int nrv = 0;
-    for (int k = 0; k < nsides; ++k)
-        nrv += prog.side_used[k] && sides[k].kind == FUSE_SIDE_ROWVEC;
     // one block per CU: most of the 160 KB of LDS can go to the column sums and the staged row vectors
     // (the streaming form keeps per-wave histograms and row totals there as well)
     const int64_t lds_budget = streaming ? std::min<int64_t>(96 * 1024, 156 * 1024 - stream_fixed) : 144 * 1024;
     // column sums: a per-block LDS vector while it fits, else fp64 atomics on the output
-    const bool col_acc = ac == 3 && rk != KIND_K;          // per-column running sums (k per column for OUTERK)
-    const bool cols_global = col_acc && n * nacck * 8 > lds_budget - 4096;
+    const bool cols_global = col_acc && !(in_lds(lds_budget) & 2);
     const bool cols_lds = col_acc && !cols_global;
-    const bool stage_rv = nrv > 0 && ((cols_lds ? n * nacck : 0) + (int64_t)nrv * n) * 8 <= lds_budget - 1024;
+    const bool stage_rv = nrv > 0 && (in_lds(lds_budget) & 1);
     const int64_t npad = (cols_lds || stage_rv) ? std::max<int64_t>(n, 1) : 1;
     const int64_t naccpad = cols_lds ? std::max<int64_t>(n * nacck, 1) : 1;
 

@@ -255,6 +255,17 @@ def test_sparse_sides_are_streamed_where_that_costs_less(F, n, mean, side, nside
     assert ("#define FUSE_XTAB 1\n" in F.last_source()) == streamed
 
 
+@pytest.mark.parametrize("n,rv", [(5000, False), (8000, False), (17000, False), (4000, True), (9000, True)])
+def test_column_sums_stay_in_lds_beside_sparse_sides(F, n, rv):
+    """Column sums (8 bytes per column, up to 17900 columns) and staged row vectors keep their place in LDS whatever form
+    the sparse sides take."""
+    m, nnz = 200000, 30000000
+    F.cache_clear()
+    F.prepare_cell_csr(XYZ if rv else XYZ[:3], (m, n), nnz, [("sparse", (0, None, nnz, (m, n))), ("rowvec", None)][:2 if rv else 1], "col")
+    src = F.last_source()
+    assert "#define FUSE_COLS_GLOBAL 0\n" in src and (not rv or "#define FUSE_STAGE_RV 1\n" in src)
+
+
 def test_row_type_checking_and_sparse_safety(F):
     dot_v = [("main",), ("side", 0), ("dot",)]
     F.prepare_row(dot_v, (100, 10), [("rowvec", None)], "none")            # scalar result, per row
