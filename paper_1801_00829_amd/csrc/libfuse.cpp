@@ -1005,7 +1005,7 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
     // non-temporal loads 770 us); 597717 x 353, 30 cells per row, log-normal lengths 1092 -> 168 us; 139891 x 122, 5.5 per
     // row 80 -> 21 us; 74111 x 1083, 190 per row 187 -> 114 us.
     // The rule compares what a batch costs with what its rows and cells cost in the other forms, in ps of the whole chip:
-    // a batch 460, 4 per 64 words and 420 per started 256 cells of a side (with 12 waves); a row 20, a cell of X 4, a cell of
+    // a batch 460, 130 per row aggregate, 4 per 64 words and 420 per started 256 cells of a side (with 12 waves); a row 20, a cell of X 4, a cell of
     // a side 1.6, 5.1 or 8 (one, two or three sides; up to 5.5 cells per row, where the other form is this skeleton with
     // bisections, 1.6 and 5 per row and side, and three quarters of it all, since matrices that fit in the caches gain
     // more there: 874 columns, 2.7 per row, 430826 rows 18 / 31 us), rows beyond 256 cells more by the square root of their
@@ -1047,7 +1047,7 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
         const double rows = mean_len > T ? 1.0 / std::ceil(mean_len / T)
                                          : std::max(1.0, std::min(std::floor(fit), (double)std::min<int64_t>(63, words * 32 / n)));
         const double cells = rows * mean_len;            // of a batch
-        double batch = 460.0 + 4.0 * words / 64, other = 20.0 * rows + 4.0 * cells;
+        double batch = 460.0 + 130.0 * prog.nred + 4.0 * words / 64, other = 20.0 * rows + 4.0 * cells;
         for (int k = 0; k < nsides; ++k)
             if (prog.side_used[k] && sides[k].kind == FUSE_SIDE_SPARSE) {
                 const double side = sides[k].sp && m > 0 ? rows * ((double)sides[k].sp->nnz / (double)m) : 0.0;
@@ -1061,7 +1061,13 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
         // 12000 273 / 1747; a row vector, 6000 columns 259 / 308, 12000 244 / 315.
         const int64_t fixed = (int64_t)(block / 64) * wave_bytes + 2048;
         const int lost = in_lds(mean_len <= 5.5 ? 96 * 1024 : 144 * 1024) & ~in_lds(std::min<int64_t>(96 * 1024, 156 * 1024 - fixed));
-        if (xtab_mode == 1 && (batch > other || lost))
+        // Row aggregates: 130 per batch each, and an array of row totals per wave, so at most three; a row beyond 256 cells
+        // searches in memory once per stage, so mean lengths up to 180.  3e7 cells in X and one side, 1000 columns, even
+        // and log-normal rows, one aggregate: 100 per row 272 / 221 and 859 / 421 us, 180 295 / 226 and 638 / 547, 240
+        // 278 / 320 and 606 / 570, 500 496 / 881; 1e7 cells, 100 per row, 2 / 3 / 4 / 8 aggregates 99 / 85, 101 / 92, 102 /
+        // 100, 109 / 234.
+        const bool reds = prog.nred > 0 && (prog.nred > 3 || mean_len > 180.0);
+        if (xtab_mode == 1 && (batch > other || lost || reds))
             tabr = 0;
         else
             BLOCK = block;

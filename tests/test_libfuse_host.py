@@ -266,6 +266,19 @@ def test_column_sums_stay_in_lds_beside_sparse_sides(F, n, rv):
     assert "#define FUSE_COLS_GLOBAL 0\n" in src and (not rv or "#define FUSE_STAGE_RV 1\n" in src)
 
 
+@pytest.mark.parametrize("nred,mean,streamed", [(1, 100, True), (1, 300, False), (1, 1000, False), (3, 50, True), (8, 100, False), (40, 100, False)])
+def test_row_aggregates_over_sparse_sides_keep_the_search_where_it_is_cheaper(F, nred, mean, streamed):
+    """Long rows with a row aggregate, and many aggregates, stay with the lane groups, whose searches run in LDS."""
+    m, n = 100000, 1000 if mean < 300 else 4000
+    expr = []
+    for i in range(nred):
+        expr += [("main",), ("const", float(i)), ("mul",), ("side", 0), ("mul",), ("rowsum",)] + ([("add",)] if i else [])
+    F.cache_clear()
+    F.prepare_row(expr + [("main",), ("mul",)], (m, n), [("sparse", (0, None, m * mean, (m, n)))],
+                  "none", nnz=m * mean)
+    assert ("#define FUSE_XTAB 1\n" in F.last_source()) == streamed
+
+
 def test_row_type_checking_and_sparse_safety(F):
     dot_v = [("main",), ("side", 0), ("dot",)]
     F.prepare_row(dot_v, (100, 10), [("rowvec", None)], "none")            # scalar result, per row
