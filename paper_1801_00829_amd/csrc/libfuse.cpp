@@ -1005,16 +1005,15 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
     // non-temporal loads 770 us); 597717 x 353, 30 cells per row, log-normal lengths 1092 -> 168 us; 139891 x 122, 5.5 per
     // row 80 -> 21 us; 74111 x 1083, 190 per row 187 -> 114 us.
     // The rule compares what a batch costs with what its rows and cells cost in the other forms, in ps of the whole chip:
-    // a batch 460, 130 per row aggregate, 4 per 64 words and 420 per started 256 cells of a side (with 12 waves); a row 20, a cell of X 4, a cell of
-    // a side 1.6, 5.1 or 8 (one, two or three sides; up to 5.5 cells per row, where the other form is this skeleton with
-    // bisections, 1.6 and 5 per row and side, and three quarters of it all, since matrices that fit in the caches gain
-    // more there: 874 columns, 2.7 per row, 430826 rows 18 / 31 us), rows beyond 256 cells more by the square root of their
-    // length.  320 calls drawn over 60 - 30000 columns, one to three sides, even and log-normal rows: 0.64 of the other
-    // forms' time in the geometric mean, at most 1.4 times in a single one.
-    // Fitted to even row lengths over 122 - 30000 columns, 1 - 200 cells per row, sides of 0.3 - 8 times X's cells (within
-    // 20 %).  sum(X*Y), other form / this one, even and log-normal row lengths: 1000 columns, 20 cells per row in both 153 /
-    // 112 and 739 / 131 us, 2 and 16 per row 76 / 96 and 82 / 100, 10 and 80 47 / 64 and 248 / 75; 10000 columns, 50 and 50
-    // 127 / 199 and 642 / 254; 3000 columns, 1000 and 1000 424 / 119 and 614 / 169.
+    // a batch 460, 130 per row aggregate, 4 per 64 words (20 in rows beyond 256 cells, which nothing runs beside) and 420
+    // per 256 cells of a side (with 12 waves); a row 20, a cell of X 4, a cell of a side 1.6, 5.1 or 8 (one, two or three
+    // sides), rows beyond 256 cells more by the square root of their length.  Up to 5.5 cells per row the other form is
+    // this skeleton with bisections: 1.6 per cell of a side and 5 per row and side, and three quarters of it all, since
+    // matrices that fit in the caches gain more there (874 columns, 2.7 per row, 430826 rows 18 / 31 us).  Fitted to even row
+    // lengths over 122 - 30000 columns, 1 - 200 cells per row, sides of 0.3 - 8 times X's cells.  sum(X*Y), other form / this
+    // one, even and log-normal row lengths: 1000 columns, 20 cells per row in both 153 / 112 and 739 / 131 us, 2 and 16 per
+    // row 76 / 96 and 82 / 100, 10 and 80 47 / 64 and 248 / 75; 10000 columns, 50 and 50 127 / 199 and 642 / 254; 3000
+    // columns, 1000 and 1000 424 / 119 and 614 / 169; 30000 columns, 300 and 300 180 / 229 and 599 / 217.
     int nsparse = 0;
     for (int k = 0; k < nsides; ++k)
         nsparse += prog.side_used[k] && sides[k].kind == FUSE_SIDE_SPARSE;
@@ -1047,11 +1046,11 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
         const double rows = mean_len > T ? 1.0 / std::ceil(mean_len / T)
                                          : std::max(1.0, std::min(std::floor(fit), (double)std::min<int64_t>(63, words * 32 / n)));
         const double cells = rows * mean_len;            // of a batch
-        double batch = 460.0 + 130.0 * prog.nred + 4.0 * words / 64, other = 20.0 * rows + 4.0 * cells;
+        double batch = 460.0 + 130.0 * prog.nred + (mean_len > T ? 20.0 : 4.0) * words / 64, other = 20.0 * rows + 4.0 * cells;
         for (int k = 0; k < nsides; ++k)
             if (prog.side_used[k] && sides[k].kind == FUSE_SIDE_SPARSE) {
                 const double side = sides[k].sp && m > 0 ? rows * ((double)sides[k].sp->nnz / (double)m) : 0.0;
-                batch += 420.0 * std::max(1.0, side / T);
+                batch += 420.0 * (mean_len > T ? side / T + 0.5 : std::max(1.0, side / T));
                 other += mean_len <= 5.5 ? 5.0 * rows + 1.6 * side : (nsparse == 1 ? 1.6 : nsparse == 2 ? 5.1 : 8.0) * side;
             }
         batch *= 768.0 / block;
