@@ -1161,9 +1161,10 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
              std::to_string(m < (1LL << 30)) + "\n#define FUSE_NPAD " +
              std::to_string(npad) + "\n#define FUSE_NACCPAD " + std::to_string(naccpad) + "\n#define FUSE_STAGE_RV " + std::to_string(stage_rv) +
              "\n#define FUSE_NRV " + std::to_string(std::max(nrv, 1)) + "\n#define FUSE_NSPARSE " + std::to_string(std::max(nsparse, 1)) +
-             "\n#define FUSE_SCAP " + std::to_string(scap) + "\n#define FUSE_XTAB " + std::to_string(xtab) +
-             "\n#define FUSE_WORDS " + std::to_string(words) +
-             "\n#define FUSE_SRP64 " + std::to_string(srp64) + "\n";
+             "\n#define FUSE_SCAP " + std::to_string(scap) + "\n";
+        if (streaming)
+            s += "#define FUSE_XTAB " + std::to_string(xtab) + "\n#define FUSE_WORDS " + std::to_string(xtab ? words : 0) +
+                 "\n#define FUSE_SRP64 " + std::to_string(xtab && srp64) + "\n";
         s += side_tables(sides, nsides, prog.side_used);
         s += emit_row_body(prog);
         s += streaming ? kSrcRowCsrStream : kSrcRowCsr;

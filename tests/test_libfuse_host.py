@@ -279,6 +279,14 @@ def test_row_aggregates_over_sparse_sides_keep_the_search_where_it_is_cheaper(F,
     assert ("#define FUSE_XTAB 1\n" in F.last_source()) == streamed
 
 
+def test_lane_group_sources_hold_nothing_of_the_streaming_form(F):
+    """A kernel's name hashes its source: what only the streaming form reads must not rename the lane groups' kernels (their
+    committed traffic figures are found by name)."""
+    F.cache_clear()
+    F.prepare_row([("main",), ("side", 0), ("dot",), ("main",), ("mul",)], (10000000, 1000), [("rowvec", None)], "col_t", nnz=100000000)
+    assert not re.search("FUSE_(XTAB|WORDS|SRP64)", F.last_source())
+
+
 def test_row_type_checking_and_sparse_safety(F):
     dot_v = [("main",), ("side", 0), ("dot",)]
     F.prepare_row(dot_v, (100, 10), [("rowvec", None)], "none")            # scalar result, per row
