@@ -509,15 +509,15 @@ int row_mfma_impl(const Program &prog, const std::string &pkey, const fuse_dense
     const int cap = !Xs ? 1 : csr_cap(pipe ? 64 : BLOCK / 16);
     const std::string key = std::string(pipe ? "rowmfmap|" : "rowmfma|") + pkey + "|" + side_key(sides, nsides) + "|v" + std::to_string(VEC) +
                             "n" + std::to_string(nct) + (pipe ? "r" + std::to_string(TR) + "l" + std::to_string(nld) : "w" + std::to_string(NWAVE)) + "nt" + std::to_string(env_int("FUSE_NT", 1)) +
-                            "m" + std::to_string(m4) + (csrx ? "csr" + std::to_string(rp64) + "c" + std::to_string(cap) : "");
+                            (pipe ? "" : "m" + std::to_string(m4)) + (csrx ? "csr" + std::to_string(rp64) + "c" + std::to_string(cap) : "");
     std::shared_ptr<Plan> plan;
     int rc = rt.plan(key, pipe ? "fuse_row_mfma_pipe" : "fuse_row_mfma", [&](const std::string &name) {
         std::string s = kSrcArgs;
         s += "#define FUSE_NT " + std::to_string(env_int("FUSE_NT", 1)) + "\n";
         s += kSrcCommon;
         s += "#define FUSE_KERNEL_NAME " + name + "\n";
-        s += "#define FUSE_M4 " + std::to_string(m4) + "\n#define FUSE_TR " + std::to_string(TR) + "\n#define FUSE_RPW " +
-             std::to_string((TR + NPROD - 1) / NPROD) + "\n";
+        s += pipe ? "#define FUSE_TR " + std::to_string(TR) + "\n#define FUSE_RPW " + std::to_string((TR + NPROD - 1) / NPROD) + "\n"
+                  : "#define FUSE_M4 " + std::to_string(m4) + "\n";
         s += "#define FUSE_CSRX " + std::to_string(csrx) + "\n#define FUSE_RP64 " + std::to_string(rp64) + "\n#define FUSE_CAP " +
              std::to_string(cap) + "\n";
         s += "#define FUSE_NWAVE " + std::to_string(pipe ? NPROD : NWAVE) + "\n#define FUSE_VEC " + std::to_string(VEC) + "\n#define FUSE_NP " + std::to_string(pipe ? np_pipe : np) +

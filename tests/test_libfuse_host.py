@@ -287,6 +287,18 @@ def test_lane_group_sources_hold_nothing_of_the_streaming_form(F):
     assert not re.search("FUSE_(XTAB|WORDS|SRP64)", F.last_source())
 
 
+def test_forms_of_the_matrix_units_hold_only_what_they_read(F, monkeypatch):
+    """The choice of products is the block form's alone: it neither renames nor multiplies the pipelined form's plans."""
+    names = set()
+    for m4 in ("0", "1"):
+        monkeypatch.setenv("FUSE_MFMA_M4", m4)
+        F.cache_clear()
+        F.prepare_row([("main",), ("main",), ("side", 0), ("matmult",), ("outerk",)], (1000000, 784), [("rhs", (784, 10))], "col_t")
+        assert F.last_kernel().startswith("fuse_row_mfma_pipe_") and "FUSE_M4" not in F.last_source()
+        names.add(F.last_kernel())
+    assert len(names) == 1
+
+
 def test_row_type_checking_and_sparse_safety(F):
     dot_v = [("main",), ("side", 0), ("dot",)]
     F.prepare_row(dot_v, (100, 10), [("rowvec", None)], "none")            # scalar result, per row
