@@ -472,7 +472,7 @@ int row_mfma_impl(const Program &prog, const std::string &pkey, const fuse_dense
         const double avg = m > 0 ? (double)Xs->nnz / (double)m : 1.0;
         return (int)std::min<int64_t>(16, std::max<int64_t>(1, (int64_t)(avg * 1.34 / threads) + 1));
     };
-    // Pipelined form (FUSE_MFMA_PIPE=0: never): 7 product waves and one for the generated code, one block per CU; the most
+    // Pipelined form (FUSE_MFMA_PIPE: 0 never, 1 by the rules here and below, 2 wherever a tile fits): 7 product waves and one for the generated code, one block per CU; the most
     // rows per tile of which four tiles fit in LDS, while V, the running sums and two travelling tiles leave a thread 60 of
     // its 256 registers.  2.4 GB, logistic regression core, block form / pipelined: n = 128 k = 4 586 / 564, k = 16
     // 1285 / 1015 us; n = 256 460 / 466, 818 / 814; n = 500 540 / 438, 718 / 674; n = 784 494 / 436, 832 / 660; n = 1000
@@ -484,7 +484,8 @@ int row_mfma_impl(const Program &prog, const std::string &pkey, const fuse_dense
     bool pipe = false;
     const int ns_ = std::max(nsides, 1), mp = (kd + 3) / 4, NPROD = 7;
     const int64_t np_pipe = nct * 16 + (40 - nct * 16 % 32) % 32;          // 8 modulo 32
-    if (env_int("FUSE_MFMA_PIPE", 1) != 0 && (!Xs || (Xs->nnz > 0 && n >= 256 && kd <= 12))) {
+    const int pipe_mode = env_int("FUSE_MFMA_PIPE", 1);
+    if (pipe_mode != 0 && (!Xs || (Xs->nnz > 0 && n >= 256 && kd <= 12))) {
         for (int tr = Xs ? 8 : 16; tr >= (Xs ? 8 : 4) && !pipe; tr >>= 1) {
             const int64_t lds = (4 * tr * np_pipe + (int64_t)(2 * NPROD + 3 + ns_) * tr * (4 * mp + 1)) * 8;
             const int64_t held = (nct + NPROD - 1) / NPROD * mp * 4;
@@ -494,6 +495,27 @@ int row_mfma_impl(const Program &prog, const std::string &pkey, const fuse_dense
                 TR = tr;
             }
         }
+    }
+    // Where the block form stays although a dense tile fits (FUSE_MFMA_PIPE=2: nowhere), block form / pipelined:
+    //  - 257 to 384 columns with 4 classes (432 without k-vector sides): its products are 4x4x4 there as well, and it has
+    //    two blocks per CU while the pipeline's tile falls to 8 rows.  1.6 GB, logistic regression core / t(X)(XV): n = 256
+    //    308 / 289 and 299 / 288, 264 308 / 337 and 298 / 328, 320 273 / 334 and 264 / 347, 384 274 / 308 and 273 / 303, 416
+    //    418 / 247 and 268 / 304, 480 367 / 242 and 363 / 242;
+    //  - 113 to 128 columns with 9 to 12 classes: 8 column tiles, two rounds for seven waves and one for eight.  n = 112
+    //    550 / 518, 113 582 / 623, 128 511 / 542 (k = 8 481 / 435, k = 16 800 / 676), 144 786 / 505;
+    //  - few rows: three more steps than tiles.  GPU time of both launches, tiles of 8 and 16 rows, logistic regression core:
+    //    1000 rows n = 256 k = 10 9.6 / 11.6, n = 500 14.2 / 16.6, 4000 rows 15.9 / 18.7 and 23.9 / 28.1, 8000 rows 25.1 /
+    //    20.6 and 27.5 / 30.3, 16000 rows n = 500 36.5 / 36.1; CSR, k = 5, 4000 rows n = 300 12.9 / 16.6, 8000 rows 21.1 /
+    //    19.0, n = 500 21.1 / 24.1.  (Three classes would take the vector form instead.)
+    const int64_t cus = rt.num_cus();
+    bool kvec = false;
+    for (int q = 0; q < nsides; ++q)
+        kvec = kvec || (prog.side_used[q] && sides[q].kind == FUSE_SIDE_KVEC);
+    if (pipe && pipe_mode == 1 && kd > 3 &&
+        ((X && kd == 4 && n > 256 && n <= (kvec ? 384 : 432)) || (X && nct == 8 && mp == 3) ||
+         (TR >= 8 && m < (nct > 28 && (kd > 8 || Xs) ? 64 : 24) * cus))) {
+        pipe = false;
+        TR = 16;
     }
     const int BLOCK = pipe ? 64 * NPROD + 64 : 64 * NWAVE;
     const int loaders = pipe ? 64 * NPROD : BLOCK;               // threads that bring the tile in
@@ -545,7 +567,10 @@ int row_mfma_impl(const Program &prog, const std::string &pkey, const fuse_dense
     const int64_t by_lds = std::max<int64_t>(1, (158 * 1024) / lds_bytes(NWAVE));
     const int64_t bpc = pipe ? 1 : std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(by_lds, 16 / NWAVE),
                                                             env_int("FUSE_MFMA_BLOCKS_PER_CU", 4)));
-    const int64_t gx = std::max<int64_t>(1, std::min<int64_t>(ntiles, (int64_t)rt.num_cus() * bpc));
+    // (pipelined: a block gets at least 16 rows, so that the partial sums stay as few as with tiles of 16 rows; 784 columns,
+    // k = 10, 1000 rows 30.7 -> 20.8 us of GPU time, block form 23.3)
+    const int64_t most = pipe ? std::max<int64_t>((m + 15) / 16, std::min<int64_t>(ntiles, 16)) : ntiles;
+    const int64_t gx = std::max<int64_t>(1, std::min<int64_t>(most, (int64_t)rt.num_cus() * bpc));
     Workspace ws;
     if ((rc = rt.workspace(stream, (size_t)gx * (size_t)(n * kd), ws, g_err)))
         return rc;
@@ -612,10 +637,13 @@ int row_dense_impl(const Program &prog, const std::string &pkey, const fuse_dens
         //  against 676 / 723, n = 1000 k = 3 516 / 547 against 594 / 609: the rule for the block form stays at 4);
         //  pipelined form (rows of 120 columns and more), 2.4 GB, logistic regression core, vector form against it: k = 3
         //  n = 128 568 / 544, 256 575 / 447, 500 509 / 434, 784 593 / 438, 1000 464 / 418, 1101 608 / 438; k = 2 n = 128
-        //  397 / 542, 256 410 / 443, 500 437 / 429, 784 428 / 431, 1000 384 / 416
+        //  397 / 542, 256 410 / 443, 500 437 / 429, 784 428 / 431, 1000 384 / 416; few rows, GPU time, k = 3: 4000 x 120 9.1 /
+        //  10.4, x 256 11.1 / 12.8, x 400 18.2 / 14.0, 8000 x 256 15.1 / 13.0
         int min_k = env_int("FUSE_MFMA_MIN_K", -1);
+        const int pipe_mode = env_int("FUSE_MFMA_PIPE", 1);          // (three classes are for the pipelined form only)
+        const bool pipe3 = n >= 120 && pipe_mode != 0 && (pipe_mode == 2 || n >= 384 || m >= 24 * (int64_t)rt.num_cus());
         if (min_k < 0)
-            min_k = !mfma_wave_form(X, launch) ? (n >= 120 ? 3 : 4) : n >= 48 ? 2 : n > 16 ? 3 : 4;
+            min_k = !mfma_wave_form(X, launch) ? (pipe3 ? 3 : 4) : n >= 48 ? 2 : n > 16 ? 3 : 4;
         const int64_t tile_bytes = (16 * ((n + 15) / 16 * 16 + 1) + (int64_t)(4 + 2 + std::max(nsides, 1)) * 272 + 128) * 8;
         if (ac == 3 && min_k > 0 && kd >= min_k && n >= 16 && tile_bytes <= 158 * 1024 &&
             mfma_pattern(prog, sides, nsides, vside))

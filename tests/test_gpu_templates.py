@@ -1111,11 +1111,12 @@ def test_row_matrix_rhs_chain_and_mlogreg_core(shape, rhs_form):
 @pytest.mark.parametrize("sparse", [False, True])
 @pytest.mark.parametrize("shape", [(1, 128, 4), (17, 120, 3), (4099, 161, 5), (8200, 300, 12), (3001, 500, 16), (2055, 541, 10),
                                    (1027, 784, 10), (5, 1001, 8), (2049, 1051, 3)])
-def test_row_matrix_rhs_pipelined(shape, sparse):
+def test_row_matrix_rhs_pipelined(shape, sparse, monkeypatch):
     """The pipelined matrix-unit form: last tiles and blocks with fewer tiles than the pipeline is long, column tiles dealt
     unevenly, padded classes, odd columns and strided rows, per-row scalars, k-vectors and a constant side at once.
     The bound: two sums of n and m products, at most (n + m + 8) * 2^-53 of the same sums of absolute values."""
     import paper_1801_00829_amd as F
+    monkeypatch.setenv("FUSE_MFMA_PIPE", "2")                  # (by itself it wants more rows than most of these have)
     m, n, k = shape
     rng = np.random.default_rng(5)
     x, v, p, c = rng.normal(size=(m, n)), rng.normal(size=(n, k)), rng.uniform(size=(m, k)), rng.uniform(size=m)
@@ -1136,6 +1137,21 @@ def test_row_matrix_rhs_pipelined(shape, sparse):
     ref = x.T @ (0.5 * c[:, None] * p * (x @ v))
     scale = np.abs(x).T @ (0.5 * c[:, None] * p * (np.abs(x) @ np.abs(v)))
     assert (np.abs(got - ref) <= 4 * (n + m + 8) * 2.0 ** -53 * scale + 1e-300).all()
+
+
+@pytest.mark.parametrize("shape", [(50, 1050, 16), (33, 1104, 13), (3001, 300, 4), (1999, 120, 10), (8199, 127, 9), (17, 384, 4)])
+def test_row_matrix_rhs_block_form_by_default(shape):
+    """Shapes that take the block form of the matrix units by themselves: 16x16x4 products at the widest rows it holds, 4x4x4
+    products, few rows.  The bound is that of the pipelined form's test."""
+    import paper_1801_00829_amd as F
+    m, n, k = shape
+    rng = np.random.default_rng(7)
+    x, v, p = rng.normal(size=(m, n)), rng.normal(size=(n, k)), rng.uniform(size=(m, k))
+    expr = [("main",), ("main",), ("side", 0), ("matmult",), ("side", 1), ("mul",), ("outerk",)]
+    got = host(F.fuse_row(expr, to_dev(x), dev_sides([("rhs", v), ("kvec", p)]), "col_t")).reshape(n, k)
+    assert F.last_kernel().rsplit("_", 1)[0] == "fuse_row_mfma"
+    scale = np.abs(x).T @ (p * (np.abs(x) @ np.abs(v)))
+    assert (np.abs(got - x.T @ (p * (x @ v))) <= 4 * (n + m + 8) * 2.0 ** -53 * scale + 1e-300).all()
 
 
 @pytest.mark.parametrize("k", [1, 3, 10, 16])

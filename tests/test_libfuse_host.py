@@ -279,6 +279,22 @@ def test_row_aggregates_over_sparse_sides_keep_the_search_where_it_is_cheaper(F,
     assert ("#define FUSE_XTAB 1\n" in F.last_source()) == streamed
 
 
+@pytest.mark.parametrize("m,n,k,kvec,form", [
+    (1000000, 784, 10, True, "fuse_row_mfma_pipe"), (1000, 784, 10, True, "fuse_row_mfma_pipe"), (1000000, 256, 4, True, "fuse_row_mfma_pipe"),
+    (1000000, 300, 5, False, "fuse_row_mfma_pipe"), (1000000, 400, 4, True, "fuse_row_mfma_pipe"), (1000000, 144, 10, True, "fuse_row_mfma_pipe"),
+    (100000, 120, 3, True, "fuse_row_mfma_pipe"), (1000, 400, 3, True, "fuse_row_mfma_pipe"), (8000, 256, 16, True, "fuse_row_mfma_pipe"),
+    (1000, 256, 10, True, "fuse_row_mfma"), (1000000, 300, 4, True, "fuse_row_mfma"), (1000000, 400, 4, False, "fuse_row_mfma"),
+    (1000000, 120, 10, True, "fuse_row_mfma"), (8000, 500, 10, True, "fuse_row_mfma"), (1000000, 1050, 16, True, "fuse_row_mfma"),
+    (4000, 120, 3, True, "fuse_row_dense"), (1000000, 100, 8, True, "fuse_row_mfma_wave")])
+def test_matrix_unit_forms_by_rows_columns_and_classes(F, m, n, k, kvec, form):
+    """Which form of t(X) f(X V) bodies a shape takes by itself."""
+    expr = [("main",)] + ([("side", 1)] if kvec else []) + [("main",), ("side", 0), ("matmult",)] + ([("mul",)] if kvec else []) + [("outerk",)]
+    F.prepare_row(expr, (m, n), [("rhs", (n, k)), ("kvec", (m, k))][:2 if kvec else 1], "col_t")
+    assert F.last_kernel().rsplit("_", 1)[0] == form
+    if form == "fuse_row_mfma_pipe":
+        assert "FUSE_M4" not in F.last_source()
+
+
 def test_lane_group_sources_hold_nothing_of_the_streaming_form(F):
     """A kernel's name hashes its source: what only the streaming form reads must not rename the lane groups' kernels (their
     committed traffic figures are found by name)."""
