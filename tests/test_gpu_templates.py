@@ -1057,15 +1057,16 @@ MLOGREG = [("main",)] + MLOG_Q + [("side", 1)] + MLOG_Q + [("rowsum",), ("mul",)
 TXXV = [("main",), ("main",), ("side", 0), ("matmult",), ("outerk",)]                     # t(X) (X V)
 
 
-@pytest.fixture(params=["vector", "matrix_units", "matrix_units_blocks"])
+@pytest.fixture(params=["vector", "matrix_units", "matrix_units_blocks", "matrix_units_pipelined"])
 def rhs_form(request, monkeypatch):
     """The forms of t(X) (f(X V)) bodies: k-vectors on the vector ALUs (k butterflies per row), or the
     two products on the fp64 matrix units (by default from 3 or 5 classes on, while 16 rows fit in LDS):
-    one wave per 16-row tile for contiguous matrices of at most 112 columns, a block per tile otherwise
-    ("matrix_units_blocks" takes the block form for the narrow matrices too)."""
+    one wave per 16-row tile for contiguous matrices of at most 112 columns, a block per tile or the pipelined
+    form otherwise ("matrix_units_blocks" / "matrix_units_pipelined" take those for all matrices)."""
     monkeypatch.setenv("FUSE_MFMA_MIN_K", "0" if request.param == "vector" else "1")
-    if request.param == "matrix_units_blocks":
+    if request.param in ("matrix_units_blocks", "matrix_units_pipelined"):
         monkeypatch.setenv("FUSE_MFMA_WAVE_FORM", "0")
+        monkeypatch.setenv("FUSE_MFMA_PIPE", "0" if request.param == "matrix_units_blocks" else "2")
     return request.param
 
 
@@ -1091,6 +1092,8 @@ def test_row_matrix_rhs_chain_and_mlogreg_core(shape, rhs_form):
         assert F.last_kernel().startswith("fuse_row_mfma_") == (rhs_form != "vector")
         if n <= 112:
             assert F.last_kernel().startswith("fuse_row_mfma_wave_") == (rhs_form == "matrix_units")
+        if rhs_form.startswith("matrix_units_"):
+            assert F.last_kernel().startswith("fuse_row_mfma_pipe_") == (rhs_form == "matrix_units_pipelined")
     got = host(F.fuse_row(MLOGREG, xd, sd, "col_t")).reshape(n, k)
     assert_close(got, plans.mlogreg_core(x, v, p), scale=2 * k * scale, what="mlogreg core")
     assert_close(got, unfused.row_dense(MLOGREG, x, [("rhs", v), ("kvec", p)], "col_t"), scale=2 * k * scale,
