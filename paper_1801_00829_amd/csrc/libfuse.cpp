@@ -701,11 +701,21 @@ int row_dense_impl(const Program &prog, const std::string &pkey, const fuse_dens
         epl64 = 1;
     const int EPL = (int)epl64;
     int RS = env_int("FUSE_ROW_RS", 0);
-    // element-wise results hold no running sums per column: two wide rows in flight.  X * column vector * row vector to a
-    // matrix, one row / two: 99991 x 1001 366 / 320 us, 100000 x 1000 320 / 306
+    // Element-wise results hold no running sums per column: two wide rows in flight, while both rows of X and of every
+    // matrix side and the row vectors take at most 440 registers and a lane at most 24 columns; rows in several stripes with
+    // at most one matrix side.  1e8 cells, one row / two, X * column vector * row vector: n = 1000 320 / 306 us, 1001 366 /
+    // 318, 1500 323 / 312, 2001 366 / 327, but 2000 (32 columns per lane) 313 / 317, 4000 323 / 325; one matrix side and a
+    // row vector: 1000 472 / 459, 1001 494 / 470, 2001 502 / 497; two: 1000 631 / 618, 2001 655 / 736; three: 1000 790 / 763,
+    // 2000 774 / 1072 (spills), 2001 818 / 887.
     const bool map_only = ac == 0 && kd == 0 && prog.nstage == 0;
+    int nmat = 0, nrvec = 0;
+    for (int k = 0; k < nsides; ++k) {
+        nmat += prog.side_used[k] && sides[k].kind == FUSE_SIDE_MATRIX;
+        nrvec += prog.side_used[k] && sides[k].kind == FUSE_SIDE_ROWVEC;
+    }
+    const bool two_wide = map_only && EPL * VEC <= 24 && (4 * (1 + nmat) + 2 * nrvec) * EPL * VEC <= 440 && (stripes == 1 || nmat <= 1);
     if (RS <= 0)
-        RS = EPL >= 8 ? (map_only ? 2 : 1) : (EPL >= 3 ? 2 : 4);
+        RS = EPL >= 8 ? (two_wide ? 2 : 1) : (EPL >= 3 ? 2 : 4);
     const int BLOCK = WPR > 1 ? std::max(128, 64 * WPR) : 256;
     if (WPR > 1 && BLOCK != 64 * WPR)
         WPR = BLOCK / 64;          // at least two waves per block
@@ -770,9 +780,12 @@ int row_dense_impl(const Program &prog, const std::string &pkey, const fuse_dens
     const int64_t rows_per_iter = WPR > 1 ? RS : (int64_t)(64 / G) * RS * NW;
     const int cus = rt.num_cus();
     int64_t gx = (m + rows_per_iter - 1) / rows_per_iter;
-    // element-wise results: three blocks per CU, 2 / 3 / 4 blocks: 99991 x 77 34 / 30.5 / 28 us, 260001 x 301 244 / 234 / 244,
-    // 99991 x 1001 320 / 322 / 327
-    const int bpc = WPR > 1 ? std::max(1, 16 / WPR) : env_int("FUSE_ROW_BLOCKS_PER_CU", map_only ? 3 : 2);
+    // element-wise results over odd rows (8-byte vectors) of fewer than 8 vectors per lane: three blocks per CU, with a matrix
+    // side only for rows of up to 32 lanes.  1e8 cells, 2 / 3 / 4 blocks, X * column vector * row vector: n = 29 343 / 326 /
+    // 359 us, 77 355 / 341 / 331, 301 312 / 300 / 315, but 50 322 / 340 / 366, 100 296 / 310 / 332, 1000 306 / 308, 1001 318 /
+    // 320 / 327, 2001 327 / 341; one matrix side and a row vector: 77 486 / 457 / 469, 301 439 / 469 / 494; two: 29 716 / 856
+    const bool three = map_only && VEC == 1 && EPL < 8 && (nmat == 0 || (nmat == 1 && G <= 32));
+    const int bpc = WPR > 1 ? std::max(1, 16 / WPR) : env_int("FUSE_ROW_BLOCKS_PER_CU", three ? 3 : 2);
     const int64_t cap = std::max<int64_t>(1, (int64_t)cus * bpc / stripes);
     gx = std::min(gx, cap);
     Workspace ws;

@@ -315,6 +315,18 @@ def test_forms_of_the_matrix_units_hold_only_what_they_read(F, monkeypatch):
     F.cache_clear()                         # (the source seen by other tests is that of the last plan compiled)
 
 
+@pytest.mark.parametrize("n,nmat,rows", [(1001, 0, 2), (1000, 3, 2), (2001, 0, 2), (2000, 0, 1), (2000, 3, 1), (2001, 2, 1), (4000, 1, 1), (1000, 7, 1)])
+def test_element_wise_rows_in_flight_fit_the_registers(F, n, nmat, rows):
+    """Two wide rows are in flight only where they and the same rows of all matrix sides stay in registers."""
+    expr = [("main",)]
+    for q in range(nmat + 1):
+        expr += [("side", q), ("mul",)]
+    F.cache_clear()
+    F.prepare_cell(expr, (1000, n), [("matrix", None)] * nmat + [("rowvec", None)], "none")
+    assert "#define FUSE_RS %d\n" % rows in F.last_source()
+    F.cache_clear()
+
+
 def test_row_type_checking_and_sparse_safety(F):
     dot_v = [("main",), ("side", 0), ("dot",)]
     F.prepare_row(dot_v, (100, 10), [("rowvec", None)], "none")            # scalar result, per row
