@@ -1049,8 +1049,9 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
     // a batch 460, 130 per row aggregate, 4 per 64 words (20 in rows beyond 256 cells, which nothing runs beside) and 420
     // per 256 cells of a side (with 12 waves); a row 20, a cell of X 4, a cell of a side 1.6, 5.1 or 8 (one, two or three
     // sides), rows beyond 256 cells more by the square root of their length.  Up to 5.5 cells per row the other form is
-    // this skeleton with bisections: 1.6 per cell of a side and 5 per row and side, and three quarters of it all, since
-    // matrices that fit in the caches gain more there (874 columns, 2.7 per row, 430826 rows 18 / 31 us).  Fitted to even row
+    // this skeleton with bisections: 5, 8.5 or 10 per row and side and 1.6, 3 or 4.4 per cell of a side, and three quarters of
+    // it all, since matrices that fit in the caches gain more there (874 columns, 2.7 per row, 430826 rows 18 / 31 us, 812
+    // columns, 2.7 per row, three sides 175 / 251; 3e6 rows, two sides, 350 columns, 1.7 per row 173 / 111, three, 168 columns, 1.9 196 / 132).  Fitted to even row
     // lengths over 122 - 30000 columns, 1 - 200 cells per row, sides of 0.3 - 8 times X's cells.  sum(X*Y), other form / this
     // one, even and log-normal row lengths: 1000 columns, 20 cells per row in both 153 / 112 and 739 / 131 us, 2 and 16 per
     // row 76 / 96 and 82 / 100, 10 and 80 47 / 64 and 248 / 75; 10000 columns, 50 and 50 127 / 199 and 642 / 254; 3000
@@ -1092,7 +1093,8 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
             if (prog.side_used[k] && sides[k].kind == FUSE_SIDE_SPARSE) {
                 const double side = sides[k].sp && m > 0 ? rows * ((double)sides[k].sp->nnz / (double)m) : 0.0;
                 batch += 420.0 * (mean_len > T ? side / T + 0.5 : std::max(1.0, side / T));
-                other += mean_len <= 5.5 ? 5.0 * rows + 1.6 * side : (nsparse == 1 ? 1.6 : nsparse == 2 ? 5.1 : 8.0) * side;
+                other += mean_len <= 5.5 ? (nsparse == 1 ? 5.0 : nsparse == 2 ? 8.5 : 10.0) * rows + (nsparse == 1 ? 1.6 : nsparse == 2 ? 3.0 : 4.4) * side
+                                         : (nsparse == 1 ? 1.6 : nsparse == 2 ? 5.1 : 8.0) * side;
             }
         batch *= 768.0 / block;
         other *= mean_len > T ? 1.5 * std::sqrt(mean_len / T) : mean_len <= 5.5 ? 0.75 : 1.0;

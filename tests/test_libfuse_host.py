@@ -246,7 +246,7 @@ def test_three_streamed_sides_run_with_the_registers_of_eight_waves(F):
 
 @pytest.mark.parametrize("n,mean,side,nsides,streamed", [
     (1000, 2, 500, 1, False), (1000, 1, 1, 1, False), (1000, 10, 80, 1, False), (10000, 10, 10, 2, False), (30000, 300, 300, 1, False),       # bisection
-    (1000, 100, 100, 2, True), (1000, 10, 10, 1, True), (122, 5, 5, 1, True), (1000, 20, 60, 2, True), (3000, 1000, 1000, 1, True)])
+    (1000, 100, 100, 2, True), (1000, 10, 10, 1, True), (122, 5, 5, 1, True), (350, 2, 2, 2, True), (1000, 2, 2, 2, False), (1000, 20, 60, 2, True), (3000, 1000, 1000, 1, True)])
 def test_sparse_sides_are_streamed_where_that_costs_less(F, n, mean, side, nsides, streamed):
     """The choice between streaming the sides' cells and searching them takes both sides' cells into account."""
     m = 200000
