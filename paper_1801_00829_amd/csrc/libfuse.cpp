@@ -476,9 +476,10 @@ int row_mfma_impl(const Program &prog, const std::string &pkey, const fuse_dense
     // rows per tile of which four tiles fit in LDS, while V, the running sums and two travelling tiles leave a thread 60 of
     // its 256 registers.  2.4 GB, logistic regression core, block form / pipelined: n = 128 k = 4 586 / 564, k = 16
     // 1285 / 1015 us; n = 256 460 / 466, 818 / 814; n = 500 540 / 438, 718 / 674; n = 784 494 / 436, 832 / 660; n = 1000
-    // 492 / 429, 1542 / 665.  CSR rows are scattered by as many waves as a tile has rows, so a tile of 4 gains nothing (784
+    // 492 / 429, 1542 / 665; 1.6 GB, strided rows: n = 16 k = 8 2725 / 1986, k = 16 2904 / 2955, n = 64 k = 8 753 / 633, n = 100
+    // k = 4 523 / 353, k = 16 1017 / 730.  CSR rows are scattered by as many waves as a tile has rows, so a tile of 4 gains nothing (784
     // columns, a quarter stored, k = 10: 1472 / 1490 us) and few columns are cheaper in the block form (112 columns, 30 %
-    // stored, k = 10: 887 / 1048; 300 columns, 20 %, k = 5 / 10: 2033 / 1395, 2070 / 1518; 500 columns, 16 %, k = 5 / 10 / 16:
+    // stored, k = 10: 887 / 1048; 300 columns, 20 %, log-normal rows, k = 5 / 10: 2033 / 1395, 2070 / 1518; 500 columns, 16 %, k = 5 / 10 / 16:
     // 1048 / 867, 1075 / 996, 1106 / 1150).
     int TR = 16;
     bool pipe = false;
@@ -615,7 +616,7 @@ int row_dense_impl(const Program &prog, const std::string &pkey, const fuse_dens
         return fail(FUSE_EDESC, "an OUTERK result needs FUSE_AGG_COL / FUSE_AGG_COL_T");
     const int kd = prog.kdim;
 
-    // matrix-unit form: from FUSE_MFMA_MIN_K classes on, while 16 rows of X fit in LDS (about 1200 columns)
+    // matrix-unit form: from FUSE_MFMA_MIN_K classes on, while 16 rows of X fit in LDS (about 1100 columns)
     {
         int vside = -1;
         // (measured against the vector form: equal at k = 4 for n = 784, 2.6x faster at k = 8 for n = 256,
@@ -635,7 +636,7 @@ int row_dense_impl(const Program &prog, const std::string &pkey, const fuse_dens
         //  462 / 470 against 481 / 490; block form: n = 256 k = 3 615 / 661 against 516 / 511 and n = 784 k = 3
         //  742 / 736 against 597 / 622, but n = 128 k = 3 570 / 644 against 659 / 734, n = 500 k = 4 630 / 672
         //  against 676 / 723, n = 1000 k = 3 516 / 547 against 594 / 609: the rule for the block form stays at 4);
-        //  pipelined form (rows of 120 columns and more), 2.4 GB, logistic regression core, vector form against it: k = 3
+        //  pipelined form, 2.4 GB, logistic regression core, vector form against it: k = 3
         //  n = 128 568 / 544, 256 575 / 447, 500 509 / 434, 784 593 / 438, 1000 464 / 418, 1101 608 / 438; k = 2 n = 128
         //  397 / 542, 256 410 / 443, 500 437 / 429, 784 428 / 431, 1000 384 / 416; few rows, GPU time, k = 3: 4000 x 120 9.1 /
         //  10.4, x 256 11.1 / 12.8, x 400 18.2 / 14.0, 8000 x 256 15.1 / 13.0
@@ -995,7 +996,13 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
     // t(X) %*% f(X %*% V) over a matrix that stores a good part of its cells (Mnist-like: a quarter): the dense
     // matrix-unit form, whose LDS tile is filled from the CSR rows; its time does not depend on the density, the
     // lane-group form's is proportional to it (FUSE_MFMA_CSR_DENSITY: least stored share in percent, default 15;
-    // FUSE_MFMA_CSR_MIN_K: least number of classes, default 5, 0 = never)
+    // FUSE_MFMA_CSR_MIN_K: least number of classes, default 5, 0 = never).  8e7 cells, logistic regression core, lane groups /
+    // block form / pipelined form: 112 columns, 30 % stored, k = 5 540 / 838 / -, k = 6 636 / 845, k = 8 1418 / 859, k = 10
+    // 2139 / 881; 15 %, k = 5 549 / 1572, k = 8 1428 / 1633, k = 10 2185 / 1695; 300 columns, 20 %, k = 5 602 / 1108 / 939, k = 6
+    // 693 / 1122 / 956, k = 8 1518 / 1120 / 953; 500 columns, 16 %, k = 5 520 / 1046 / 872, k = 8 1440 / 1062 / 874; 25 %, k = 5
+    // 633 / 703 / 531; 560 columns, 30 %, k = 5 569 / 589 / 455; 784 columns, 15 %, k = 5 771 / 954, k = 6 814 / 963, k = 8 1695 /
+    // 998; 25 %, k = 5 630 / 616.  So with 5 and 6 classes the lane groups are up to three times faster where less than about a
+    // quarter is stored: the line at 5 classes is right for a quarter and more only.
     {
         int vside = -1;
         const int min_k = env_int("FUSE_MFMA_CSR_MIN_K", 5);
