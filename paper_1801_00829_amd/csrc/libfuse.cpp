@@ -506,7 +506,7 @@ int row_mfma_impl(const Program &prog, const std::string &pkey, const fuse_dense
     //    550 / 518, 113 582 / 623, 128 511 / 542 (k = 8 481 / 435, k = 16 800 / 676), 144 786 / 505;
     //  - few rows: three more steps than tiles.  GPU time of both launches, tiles of 8 and 16 rows, logistic regression core:
     //    1000 rows n = 256 k = 10 9.6 / 11.6, n = 500 14.2 / 16.6, 4000 rows 15.9 / 18.7 and 23.9 / 28.1, 8000 rows 25.1 /
-    //    20.6 and 27.5 / 30.3, 16000 rows n = 500 36.5 / 36.1; CSR, k = 5, 4000 rows n = 300 12.9 / 16.6, 8000 rows 21.1 /
+    //    20.6 and 27.5 / 30.3, 16000 rows n = 500 36.5 / 36.1; 5000 rows n = 120 11.9 / 13.4, n = 300 23.5 / 21.5; CSR, k = 5, 4000 rows n = 300 12.9 / 16.6, 8000 rows 21.1 /
     //    19.0, n = 500 21.1 / 24.1.  (Three classes would take the vector form instead.)
     const int64_t cus = rt.num_cus();
     bool kvec = false;
@@ -514,7 +514,7 @@ int row_mfma_impl(const Program &prog, const std::string &pkey, const fuse_dense
         kvec = kvec || (prog.side_used[q] && sides[q].kind == FUSE_SIDE_KVEC);
     if (pipe && pipe_mode == 1 && kd > 3 &&
         ((X && kd == 4 && n > 256 && n <= (kvec ? 384 : 432)) || (X && nct == 8 && mp == 3) ||
-         (TR >= 8 && m < (nct > 28 && (kd > 8 || Xs) ? 64 : 24) * cus))) {
+         (TR >= 8 && m < (nct >= 28 && (kd > 8 || Xs) ? 64 : n <= 128 || (kd <= 4 && n <= 256) ? 24 : 16) * cus))) {
         pipe = false;
         TR = 16;
     }
