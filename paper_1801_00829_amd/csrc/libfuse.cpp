@@ -1053,8 +1053,8 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
     // non-temporal loads 770 us); 597717 x 353, 30 cells per row, log-normal lengths 1092 -> 168 us; 139891 x 122, 5.5 per
     // row 80 -> 21 us; 74111 x 1083, 190 per row 187 -> 114 us.
     // The rule compares what a batch costs with what its rows and cells cost in the other forms, in ps of the whole chip:
-    // a batch 460, 130 per row aggregate, 4 per 64 words (20 in rows beyond 256 cells, which nothing runs beside) and 420
-    // per 256 cells of a side (with 12 waves); a row 20, a cell of X 4, a cell of a side 1.6, 5.1 or 8 (one, two or three
+    // a batch 460, 130 per row aggregate, 4 per 64 words (30 in rows beyond 256 cells, which nothing runs beside) and 420
+    // per 256 cells of a side (520 after the first 256, which alone travel ahead; with 12 waves); a row 20, a cell of X 4, a cell of a side 1.6, 5.1 or 8 (one, two or three
     // sides), rows beyond 256 cells more by the square root of their length.  Up to 5.5 cells per row the other form is
     // this skeleton with bisections: 5, 8.5 or 10 per row and side and 1.6, 3 or 4.4 per cell of a side, and three quarters of
     // it all, since matrices that fit in the caches gain more there (874 columns, 2.7 per row, 430826 rows 18 / 31 us, 812
@@ -1067,7 +1067,7 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
     for (int k = 0; k < nsides; ++k)
         nsparse += prog.side_used[k] && sides[k].kind == FUSE_SIDE_SPARSE;
     int tabr = 0, words = 0;
-    auto tab_bytes = [](int w) { return (int64_t)w * 8 + (w >= 256 ? 64 * 16 : 0); };      // (the lanes' parts are padded)
+    auto tab_bytes = [](int w) { return (int64_t)w * 8 + (w >= 256 && w != 384 ? 64 * 16 : 0); };      // (the lanes' parts are padded)
     bool srp64 = false;
     for (int k = 0; k < nsides; ++k)
         srp64 |= prog.side_used[k] && sides[k].kind == FUSE_SIDE_SPARSE && sides[k].sp && sides[k].sp->rowptr_is64;
@@ -1077,7 +1077,7 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
         tabr = (int)std::min<double>(63.0, std::max(1.0, std::ceil(1.25 * fit)));
         tabr = (int)std::min<int64_t>(tabr, 32 * 1024 / n);
         words = (int)((tabr * n + 31) / 32);
-        words = std::max(64, next_pow2(words));          // (so one operator has at most five plans of this form)
+        words = words > 256 && words <= 384 ? 384 : std::max(64, next_pow2(words));          // (at most six plans of an operator)
         const int64_t wave_bytes = (64 * SC + 4) * 4 + std::max(prog.nred, 1) * 65 * 8 + tab_bytes(words) + nsparse * 64 * SC * 8;
         // 12 waves per block leave a lane 168 registers, and so do 9 to 11; 8 leave 256.  The cells of two sides on their way
         // just fit in 168 beside full and row aggregates with at most one aggregate per row (18 spilled), but not beside
@@ -1089,17 +1089,17 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
         bool narrow = nsparse == 2 && (ac == 1 || ac == 2 || !prog.result_vec) && prog.nred <= 1;
         for (int k = 0; k < nsides; ++k)
             narrow = narrow && !(prog.side_used[k] && sides[k].kind == FUSE_SIDE_MATRIX);
-        const int64_t waves = 120 * 1024 / wave_bytes;
+        const int64_t waves = (col_acc || nrv > 0 ? 120 : 148) * 1024 / wave_bytes;          // (room for column sums and row vectors)
         int block = env_int("FUSE_CSR_XTAB_BLOCK", nsparse == 1 || (narrow && waves >= 12) ? 768 : 512);
         block = (int)std::max<int64_t>(64, std::min<int64_t>(block, waves * 64));
         const double rows = mean_len > T ? 1.0 / std::ceil(mean_len / T)
                                          : std::max(1.0, std::min(std::floor(fit), (double)std::min<int64_t>(63, words * 32 / n)));
         const double cells = rows * mean_len;            // of a batch
-        double batch = 460.0 + 130.0 * prog.nred + (mean_len > T ? 20.0 : 4.0) * words / 64, other = 20.0 * rows + 4.0 * cells;
+        double batch = 460.0 + 130.0 * prog.nred + (mean_len > T ? 30.0 : 4.0) * words / 64, other = 20.0 * rows + 4.0 * cells;
         for (int k = 0; k < nsides; ++k)
             if (prog.side_used[k] && sides[k].kind == FUSE_SIDE_SPARSE) {
                 const double side = sides[k].sp && m > 0 ? rows * ((double)sides[k].sp->nnz / (double)m) : 0.0;
-                batch += 420.0 * (mean_len > T ? side / T + 0.5 : std::max(1.0, side / T));
+                batch += mean_len > T ? 420.0 * (side / T + 0.5) : 420.0 + 520.0 * std::max(0.0, side / T - 1.0);
                 other += mean_len <= 5.5 ? (nsparse == 1 ? 5.0 : nsparse == 2 ? 8.5 : 10.0) * rows + (nsparse == 1 ? 1.6 : nsparse == 2 ? 3.0 : 4.4) * side
                                          : (nsparse == 1 ? 1.6 : nsparse == 2 ? 5.1 : 8.0) * side;
             }

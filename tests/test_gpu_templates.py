@@ -1022,7 +1022,7 @@ def test_sparse_sides_streamed_with_the_rows(m, n, mean, nsparse):
     np.testing.assert_allclose(got, unfused.cell_csr(expr, x, dense, "none")[order], rtol=1e-15, atol=0)
 
 
-@pytest.mark.parametrize("n,mean,words", [(30, 20.0, 64), (100, 13.0, 128), (300, 20.0, 256), (500, 18.0, 512), (1000, 12.0, 1024), (20011, 4.0, 1024)])
+@pytest.mark.parametrize("n,mean,words", [(30, 20.0, 64), (100, 13.0, 128), (300, 20.0, 256), (500, 18.0, 384), (700, 18.0, 512), (1000, 12.0, 1024), (20011, 4.0, 1024)])
 def test_sparse_sides_streamed_bit_set_sizes(n, mean, words, monkeypatch):
     """Every size of the streaming form's bit set (lanes with one, two and up to 16 words, their parts side by side or apart),
     keys in the first and the last column, and batches in which X stores nothing beside full rows of the side."""
