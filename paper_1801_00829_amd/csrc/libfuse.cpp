@@ -1049,9 +1049,9 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
     // Sparse side inputs: the streaming skeleton with the bit set over the keys of a batch's rows (FUSE_CSR_XTAB: 0
     // never, 1 by this rule, 2 whenever it can run).  At most three such sides (their cells travel in registers); as many
     // rows per batch as its T slots hold at the mean row length, while their keys fit 1024 words (8 KB per wave).  Against
-    // the lane groups' bisection in LDS: 1e6 x 1000, a tenth stored in three matrices 1134 -> 662 us (8 waves 757 us;
-    // non-temporal loads 770 us); 597717 x 353, 30 cells per row, log-normal lengths 1092 -> 168 us; 139891 x 122, 5.5 per
-    // row 80 -> 21 us; 74111 x 1083, 190 per row 187 -> 114 us.
+    // the lane groups' bisection in LDS: 1e6 x 1000, a tenth stored in three matrices 1134 -> 661 us (8 waves 757 us;
+    // non-temporal loads 770 us); 597717 x 353, 30 cells per row, log-normal lengths 1119 -> 178 us; 139891 x 122, 5.6 per
+    // row, log-normal 78 -> 22 us; 74111 x 1083, 190 per row 188 -> 116 us.
     // The rule compares what a batch costs with what its rows and cells cost in the other forms, in ps of the whole chip:
     // a batch 460, 130 per row aggregate, 4 per 64 words (30 in rows beyond 256 cells, which nothing runs beside) and 420
     // per 256 cells of a side (520 after the first 256, which alone travel ahead; with 12 waves); a row 20, a cell of X 4, a cell of a side 1.6, 5.1 or 8 (one, two or three
