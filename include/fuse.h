@@ -269,14 +269,15 @@ int fuse_row(const fuse_expr *expr, const fuse_dense *Xd, const fuse_csr *Xs,
  *                  The library first transposes X into its workspace (a counting sort
  *                  by column, a few small kernels on the same stream; about 28 bytes
  *                  per stored cell) and then walks the columns like
- *                  RIGHT_MM walks the rows; the cells of a column are added in the order
- *                  the sort's atomics left them in, which is not fixed from run to run.
+ *                  RIGHT_MM walks the rows; the cells of a column are ordered by groups of rows,
+ *                  inside a group as the sort's atomics left them, which is not fixed from run to run.
  *                  rows(X) < 2^27 (else a scatter with fp64 atomics on the output).
  * 1 <= r <= 1024.  When V is larger than a few MB, FULL and NONE first build a table of
  * per-row offsets into column panels in the library's workspace (one more kernel on
  * the same stream; (P+1) x rows(X) offsets, P <= 1024 panels) and rely on the
- * ascending column indices the CSR format prescribes; with other column orders the
- * result is undefined (but no access leaves the arrays). */
+ * ascending column indices the CSR format prescribes for their speed (a row with
+ * another order is taken as one panel).  RIGHT_MM and LEFT_MM do so too from rank 80 on
+ * where the factor whose rows they add is larger than 12 MB. */
 int fuse_outer(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, const fuse_dense *V,
                const fuse_side *sides, int nsides, int agg, double *out, void *stream);
 

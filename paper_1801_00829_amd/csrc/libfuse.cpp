@@ -1482,6 +1482,18 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
     for (int q = 0; q < nsides; ++q)
         need_col |= prog.side_used[q] && (sides[q].kind == FUSE_SIDE_MATRIX || sides[q].kind == FUSE_SIDE_ROWVEC);
 
+    // left_mm: by default over the transposed pattern of X (built per call in the workspace) as the right_mm
+    // traversal with U and V exchanged; FUSE_OUTER_LEFT_TRANSPOSE=0 keeps the scatter with fp64 atomics
+    if (with_pattern && (mode != 3 || X->rows > 2147483647LL / 16))
+        return fail(FUSE_EUNSUPPORTED, "a prepared pattern serves left_mm of a matrix with fewer than 2^27 rows");
+    if (with_pattern && launch && !pattern && X->nnz > 0)
+        return fail(FUSE_EINVAL, "pattern is NULL");
+    const bool transposed = with_pattern || (mode == 3 && env_int("FUSE_OUTER_LEFT_TRANSPOSE", 1) != 0 && X->rows <= 2147483647LL / 16);
+    const int kmode = transposed ? 2 : mode;
+    // the matrix that the kernel walks: its rows and columns, and the factor whose rows are gathered
+    const int64_t wrows = transposed ? X->cols : X->rows, wcols = transposed ? X->rows : X->cols;
+    const fuse_dense *G_ = transposed ? U : V;
+
     // Column panels of V: worth it when V overflows an L2 and a row still has a few cells per panel.
     // Measured on 1e5 x 1e5, 100 cells per row, rank 100 (V = 80 MB): 8 to 16 panels are best; more
     // panels raise the L2 hit rate of the V gathers but stream U once more per panel.
@@ -1507,7 +1519,7 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
             }
         }
     }
-    const bool panels = npanels > 0;
+    bool panels = npanels > 0;
     if (panels) {
         UNR = env_int("FUSE_OUTER_PANEL_UNR", 2);
         UNR = std::max(1, std::min(UNR, G));
@@ -1556,12 +1568,61 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
             }
         }
     }
+    // Row runs (FUSE_OUTER_RUNS: 0 never, 1 by this rule, 2 wherever a row fits a wave), products only: a whole wave per cell,
+    // the rows of the result beside those of U in LDS.  Its time goes by cells, whatever their rows hold, and V crosses the fabric
+    // once per round of rows; the row mapping's goes by bytes gathered past L2.  Row mapping / this form, us, both factors
+    // gathered (right_mm, left_mm over a prepared pattern): 1e5 x 1e5, rank 100, 100 cells per row 1190 / 747 and 1188 / 753,
+    // 50 cells and 3e4 columns 547 / 373 and 579 / 391; 6e4 x 6e4, rank 90, 100 cells 640 / 441; 1.2e5 x 5e4, rank 110 1013 / 665;
+    // 1e5 x 1.5e4, rank 110 609 / 441; 2e4 x 4e4, rank 100 224 / 165 and 209 / 175; 2.7e4 x 1.2e5, rank 80 270 / 234 and 266 / 261;
+    // but rank 64 at 1e5 x 1e5 562 / 561, rank 76 and 12 MB 151 / 160, 20 cells per row (2 per run) 275 / 284, 0.57 million cells
+    // 50 / 71.
+    // (full_agg and no_agg, rank 100: 558 / 622 and 618 / 662 against the form above, which sums no products.)
+    const int runs_mode = env_int("FUSE_OUTER_RUNS", 1);
+    int runs_rb = 0;
+    if (runs_mode != 0 && panel_mode != 0 && kmode != 3 && (kmode == 2 || runs_mode == 2) && wrows > 0 && wcols > 0 && nvec <= 128 / VEC &&
+        (wcols - 1) * G_->ld + r < ((int64_t)1 << 28)) {          // (32-bit offsets into the gathered factor)
+        const int64_t row_bytes = nvec * VEC * 8 * (kmode == 2 ? 2 : 1);
+        const int64_t cell_bytes = X->rowptr_is64 ? 8 : 4;
+        // (beside the rows: the books of four panels, the block's sum)
+        const int64_t cap = std::min<int64_t>(256, ((int64_t)160 * 1024 - 256) / (row_bytes + 4 * (4 + cell_bytes)));
+        const int64_t blocks = std::max<int64_t>(8, rt.num_cus() / 8 * 8);
+        const int64_t rounds = (wrows + blocks * cap - 1) / (blocks * cap);
+        int64_t rb = (wrows + rounds * blocks - 1) / (rounds * blocks);
+        if (env_int("FUSE_OUTER_RB", 0) > 0)
+            rb = std::min<int64_t>(cap, env_int("FUSE_OUTER_RB", 0));
+        const int64_t vbytes = wcols * G_->ld * 8;
+        const double per_row = (double)X->nnz / (double)wrows;
+        // Columns per panel: a wave's share of a panel comes in units of up to 64 cells, about 50 of them leave room for the
+        // shares' spread; as many units as make 4.5 MB of V, at most 8 MB.  1e5 x 1e5, rank 100, 4 / 5 / 6.5 / 8 / 10 MB: 781 / 727 / 744 /
+        // 806 / 864 us; 2.7e4 x 1.2e5, rank 80: 225 / 227 / 212 / 206 / 217; 20 cells per row: 348 / 309 / 269 / 267 / 253.
+        double w = (double)wcols * 50.0 * (SBLOCK / 64) / std::max(1.0, per_row * (double)rb);
+        w *= std::max(1.0, std::ceil(4.5e6 / (w * (double)(G_->ld * 8))));
+        const int64_t pkb = env_int("FUSE_OUTER_RPANEL_KB", 0);
+        w = pkb > 0 ? (double)(pkb * 1024) / (double)(G_->ld * 8) : std::min(w, 8.0e6 / (double)(G_->ld * 8));
+        const int64_t grain = !transposed ? 1 : transpose_row_grain(X->rows, X->cols, X->nnz);
+        if (grain > 0 && (vbytes > (int64_t)env_int("FUSE_OUTER_PANEL_MIN_KB", 12288) * 1024 || panel_mode == 2)) {
+            int64_t W = std::max<int64_t>(1, std::min<int64_t>((int64_t)w, panel_mode == 2 ? (wcols + 7) / 8 : wcols));
+            W = std::max<int64_t>(grain, (W + grain / 2) / grain * grain);
+            W = std::max<int64_t>(W, (wcols + 1023) / 1024);
+            W = (W + grain - 1) / grain * grain;
+            const int64_t P = (wcols + W - 1) / W;
+            if (P >= 2 && (P + 1) * wrows * cell_bytes <= ((int64_t)1 << 30) &&
+                (runs_mode == 2 || panel_mode == 2 || (per_row / (double)P >= 3.0 && r >= 80 && X->nnz >= 1500000))) {
+                runs_rb = (int)rb;
+                npanels = (int)P;
+                panel_w = (int)W;
+            }
+        }
+    }
     // Flat form of the panel walk (FUSE_OUTER_FLAT, default 1): a wave takes RC rows at a time and deals their
     // cells inside the panel to its lane groups as one list; the chunk's U rows are staged in LDS.  RC: about 50
     // cells per chunk and panel (a round of the wave holds 64), a power of two <= 16; the staged rows of a block
     // (waves x RC x rank doubles) must fit in 60 KB.
     int flat_rc = 0;
-    if (panels && !stat_rcw && env_int("FUSE_OUTER_FLAT", 1) != 0 &&
+    panels = npanels > 0;
+    if (runs_rb)
+        stat_rcw = 0;
+    if (panels && !stat_rcw && !runs_rb && env_int("FUSE_OUTER_FLAT", 1) != 0 &&
         (panel_mode == 2 || (double)X->nnz / (double)X->rows / (double)npanels <= 16.0)) {
         const double per_row_panel = (double)X->nnz / (double)X->rows / (double)npanels;
         int rc = env_int("FUSE_OUTER_RC", 0);
@@ -1578,21 +1639,13 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
             flat_rc = rc;
     }
 
-    // left_mm: by default over the transposed pattern of X (built per call in the workspace) as the right_mm
-    // traversal with U and V exchanged; FUSE_OUTER_LEFT_TRANSPOSE=0 keeps the scatter with fp64 atomics
-    if (with_pattern && (mode != 3 || X->rows > 2147483647LL / 16))
-        return fail(FUSE_EUNSUPPORTED, "a prepared pattern serves left_mm of a matrix with fewer than 2^27 rows");
-    if (with_pattern && launch && !pattern && X->nnz > 0)
-        return fail(FUSE_EINVAL, "pattern is NULL");
-    const bool transposed = with_pattern || (mode == 3 && env_int("FUSE_OUTER_LEFT_TRANSPOSE", 1) != 0 && X->rows <= 2147483647LL / 16);
-    const int kmode = transposed ? 2 : mode;
     const bool out_vec = vec2 && (!launch || aligned16(out));
     const int flat_wpe = std::max(1, std::min(8, env_int("FUSE_OUTER_WPE", 2)));      // waves per SIMD the flat form is built for (3: spills, 898 against 810 us)
-    const int KBLOCK = stat_rcw ? SBLOCK : BLOCK;                // threads per block of the main kernel
+    const int KBLOCK = stat_rcw || runs_rb ? SBLOCK : BLOCK;                // threads per block of the main kernel
     int sunr = env_int("FUSE_OUTER_SUNR", SBLOCK > 512 ? 1 : 2);  // steps of a wave whose gathers leave together (stationary form)
     sunr = (sunr >= 2 && G % 2 == 0) ? 2 : 1;
     const int uq = std::max(1, std::min(16, env_int("FUSE_OUTER_UQ", 4)));      // vectors of U per thread in flight while the rows are staged
-    const std::string key = std::string("outer|") + (panels ? (stat_rcw ? "stat" + std::to_string(stat_rcw) + "r" + std::to_string(r) + "u" + std::to_string(sunr) + "q" + std::to_string(uq) + "|"
+    const std::string key = std::string("outer|") + (panels ? (runs_rb ? "runs" + std::to_string(runs_rb) + "r" + std::to_string(r) + "|" : stat_rcw ? "stat" + std::to_string(stat_rcw) + "r" + std::to_string(r) + "u" + std::to_string(sunr) + "q" + std::to_string(uq) + "|"
                                                              : flat_rc ? "flat" + std::to_string(flat_rc) + "r" + std::to_string(r) + "w" + std::to_string(flat_wpe) + "|" : std::string("panels|")) : std::string("")) + prog.key + "|" + side_key(sides, nsides) + "|agg" +
                             std::to_string(kmode) + (transposed ? "T" : "") + (kmode == 2 && out_vec ? "o" : "") + "|v" + std::to_string(VEC) + "g" + std::to_string(G) + "e" +
                             std::to_string(EPL) + "u" + std::to_string(UNR) + "b" + std::to_string(KBLOCK) + "w" +
@@ -1607,10 +1660,10 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
              "\n#define FUSE_VEC " + std::to_string(VEC) + "\n#define FUSE_UNR " + std::to_string(UNR) +
              "\n#define FUSE_BLOCK " + std::to_string(KBLOCK) + "\n#define FUSE_MODE " +
              std::to_string(kmode) + "\n#define FUSE_TRANSPOSED " + std::to_string(transposed) + "\n#define FUSE_OUT_VEC " + std::to_string(out_vec) + "\n#define FUSE_RP64 " + std::to_string(X->rowptr_is64 != 0) +
-             "\n#define FUSE_NEED_COL " + std::to_string(need_col) + "\n#define FUSE_PANELS " + std::to_string(panels ? (stat_rcw ? 3 : flat_rc ? 2 : 1) : 0) +
+             "\n#define FUSE_NEED_COL " + std::to_string(need_col) + "\n#define FUSE_PANELS " + std::to_string(panels ? (runs_rb ? 4 : stat_rcw ? 3 : flat_rc ? 2 : 1) : 0) +
              "\n#define FUSE_RANK " + std::to_string(r) + "\n#define FUSE_RC " + std::to_string(std::max(flat_rc, 1)) +
-             "\n#define FUSE_RB " + std::to_string(std::max(stat_rcw, 1)) + "\n#define FUSE_SUNR " + std::to_string(sunr) +
-             "\n#define FUSE_WPE " + std::to_string(stat_rcw ? SBLOCK / 256 : flat_wpe) + "\n#define FUSE_UQ " + std::to_string(uq) + "\n";
+             "\n#define FUSE_RB " + std::to_string(std::max(std::max(runs_rb, stat_rcw), 1)) + "\n#define FUSE_SUNR " + std::to_string(sunr) +
+             "\n#define FUSE_WPE " + std::to_string(stat_rcw || runs_rb ? SBLOCK / 256 : flat_wpe) + "\n#define FUSE_UQ " + std::to_string(uq) + "\n";
         s += side_tables(sides, nsides, prog.side_used);
         s += emit_outer_body(prog);
         s += kSrcOuter;
@@ -1632,7 +1685,7 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
         return rc;
     const int cus = rt.num_cus();
     const int NW = BLOCK / 64;
-    int64_t gx = ((transposed ? X->cols : X->rows) + NW - 1) / NW;
+    int64_t gx = (wrows + NW - 1) / NW;
     gx = std::max<int64_t>(1, std::min<int64_t>(gx, (int64_t)cus * env_int("FUSE_OUTER_BLOCKS_PER_CU", 8)));
     size_t pp_doubles = 0;
     if (panels) {
@@ -1640,21 +1693,20 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
         // step with their XCD and evict the panel the others are using
         int bpc = env_int("FUSE_OUTER_PANEL_BLOCKS_PER_CU", 0);
         if (bpc <= 0)
-            bpc = stat_rcw ? 1 : rt.resident_blocks_per_cu(fn.main, KBLOCK);
+            bpc = stat_rcw || runs_rb ? 1 : rt.resident_blocks_per_cu(fn.main, KBLOCK);
         gx = std::max<int64_t>(8, (int64_t)cus * bpc / 8 * 8);
-        pp_doubles = (size_t)(npanels + 1) * (size_t)X->rows * (X->rowptr_is64 ? 8 : 4) / 8 + 1;
+        pp_doubles = ((size_t)(npanels + 1) * (size_t)wrows * (X->rowptr_is64 ? 8 : 4) / 8 + 2) / 2 * 2;
     }
     const size_t part_doubles = ((size_t)gx + 15) / 16 * 16;
     // transposed matrix: scratch of the counting sort, column offsets, row and value of every cell
     const size_t rpb = X->rowptr_is64 ? 8 : 4;
     auto dbl = [](size_t bytes) { return (bytes + 15) / 16 * 2; };           // doubles, 16-byte granules
-    const size_t t_scratch = transposed ? dbl(transpose_scratch_bytes(X->rows, X->cols, X->nnz, X->rowptr_is64)) : 0,
+    const size_t t_scratch = transposed && !with_pattern ? dbl(transpose_scratch_bytes(X->rows, X->cols, X->nnz, X->rowptr_is64)) : 0,
                  t_ptr = dbl((size_t)(X->cols + 1) * rpb), t_row = dbl((size_t)X->nnz * 4),
                  t_val = (size_t)X->nnz;
-    if (transposed)
-        pp_doubles = with_pattern ? 0 : t_scratch + t_ptr + t_row + t_val;
+    const size_t t_doubles = transposed && !with_pattern ? t_scratch + t_ptr + t_row + t_val : 0;
     Workspace ws;
-    if ((rc = rt.workspace(stream, part_doubles + pp_doubles, ws, g_err)))
+    if ((rc = rt.workspace(stream, part_doubles + pp_doubles + t_doubles, ws, g_err)))
         return rc;
     fuse_kargs A;
     std::memset(&A, 0, sizeof A);
@@ -1687,7 +1739,7 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
         A.ldu = V->ld;
         A.ldv = U->ld;
     } else if (transposed) {
-        double *base = ws.partials + part_doubles;
+        double *base = ws.partials + part_doubles + pp_doubles;
         void *scratch = base, *tptr = base + t_scratch;
         int *trow = reinterpret_cast<int *>(base + t_scratch + t_ptr);
         double *tval = base + t_scratch + t_ptr + t_row;
@@ -1710,11 +1762,19 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
         A.npanels = npanels;
         A.panel_w = panel_w;
         A.panel_ptr = ws.partials + part_doubles;
-        const int64_t gp = (X->rows * 16 + 255) / 256;                 // 16 lanes per row
+        if (fn.rows) {
+            // a run of more than a wave's even share of its block's cells holds the block up: rows of a quarter more than that
+            A.long_rows = ws.ticket + 16;
+            A.row_limit = runs_mode == 2 ? X->nnz : (int64_t)(1.25 * (double)X->nnz / (double)wrows * (double)std::max(runs_rb, KBLOCK / 64) / (double)(KBLOCK / 64)) + 16;
+        }
+        const int64_t gp = (wrows * 16 + 255) / 256;                 // 16 lanes per row
         if ((rc = rt.launch(fn.prep, (unsigned)gp, 1, 256, stream, &A, sizeof A, g_err)))
             return rc;
     }
-    return rt.launch(fn.main, (unsigned)gx, 1, KBLOCK, stream, &A, sizeof A, g_err);
+    if ((rc = rt.launch(fn.main, (unsigned)gx, 1, KBLOCK, stream, &A, sizeof A, g_err)) || !fn.rows)
+        return rc;
+    const int64_t gr = std::max<int64_t>(1, std::min<int64_t>((wrows + 3) / 4, (int64_t)cus * env_int("FUSE_OUTER_BLOCKS_PER_CU", 8)));
+    return rt.launch(fn.rows, (unsigned)gr, 1, 256, stream, &A, sizeof A, g_err);
 }
 
 // values_only: the pattern exists, only the values of X are brought into its order again

@@ -26,6 +26,7 @@ struct Plan {
         hipFunction_t combine = nullptr;    // fuse_combine_cols
         hipFunction_t fill = nullptr;       // fuse_fill
         hipFunction_t prep = nullptr;       // fuse_outer_prep (Outer plans with column panels only)
+        hipFunction_t rows = nullptr;       // fuse_outer_rows (Outer products over row runs only)
     };
     std::map<int, Loaded> per_device;
 };
@@ -123,6 +124,10 @@ int check_csr_launch(const void *rowptr, int rowptr_is64, const int *colidx, lon
 size_t transpose_scratch_bytes(long long m, long long n, long long nnz, int rowptr_is64);
 int transpose_launch(const void *rowptr, int rowptr_is64, const int *colidx, const double *vals, long long m, long long n,
                      long long nnz, void *scratch, void *tptr, int *trow, double *tval, hipStream_t stream);
+
+// Within a column of the transposed matrix the cells are ordered by groups of this many rows of the original one
+// (and not inside a group); 0: not at all.
+long long transpose_row_grain(long long m, long long n, long long nnz);
 
 int iota_launch(double *dst, long long n, hipStream_t stream);     // dst[i] = (double)i
 int gather_launch(double *dst, const double *src, const double *perm, long long n, hipStream_t stream);   // dst[i] = src[perm[i]]

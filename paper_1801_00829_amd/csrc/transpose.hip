@@ -6,11 +6,12 @@
 //   1. the columns are cut into at most 1024 ranges of 2^s columns; blocks of rows count their
 //      cells per range (LDS histogram), an exclusive scan over (range, block) gives every block
 //      its place in every range, and the blocks write (column, row, value) there;
-//   2. one block per range counts its cells per column (LDS), scans the counts -- these are the
-//      column offsets of the transposed matrix -- and moves (row, value) to their final places.
+//   2. one block per range counts its cells per column and group of rows (LDS), scans the counts -- their entries at
+//      the first group are the column offsets of the transposed matrix -- and moves (row, value) to their final places.
 // Matrices with more than 1024 * 8192 columns take the plain form instead: one global atomic per
-// cell for the counts and one for the places.  The order of the cells inside a column is
-// whatever the atomics produce.
+// cell for the counts and one for the places.  The order of the cells of a column inside a group of rows (in the
+// plain form: inside the column) is whatever the atomics produce.  The groups -- as many as the counters have room for, at most
+// 128 -- let the column-panel kernels of Outer walk the result: a panel is a whole number of groups.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -147,6 +148,8 @@ constexpr int RANGE_THREADS = 1024;       // level 2
 constexpr int PART_THREADS = 1024;        // level 1: 64 rows in flight per block
 constexpr int MAX_RANGES = 1024;
 constexpr int MAX_RANGE_SHIFT = 13;       // 8192 columns per range: 32 KB of LDS counters
+constexpr int RANGE_COUNTERS = 15360;     // ... and what columns x groups of rows may take (60 KB: two blocks per CU)
+constexpr int MAX_GROUPS = 128;
 
 // level 1, counting: hist[range * nblk + block] = cells of the block's rows in the column range
 template <typename RP, typename XRP>
@@ -211,36 +214,38 @@ __global__ void __launch_bounds__(PART_THREADS) part_move_kernel(const XRP *__re
 template <typename RP>
 __global__ void __launch_bounds__(RANGE_THREADS) range_sort_kernel(const Cell *__restrict__ cells, const RP *__restrict__ place,
                                                                   const RP *__restrict__ total, long long nblk, int shift,
-                                                                  long long n, long long nnz, RP *__restrict__ tptr,
+                                                                  int groups, int group_shift, long long n, long long nnz, RP *__restrict__ tptr,
                                                                   int *__restrict__ trow, double *__restrict__ tval)
 {
-    extern __shared__ unsigned int colcnt[];          // 2^shift counters, then cursors
-    const int width = 1 << shift;
+    extern __shared__ unsigned int colcnt[];          // 2^shift columns x groups of rows: counters, then cursors
+    const int width = 1 << shift, counters = width * groups;
     const long long b = blockIdx.x;
     long long s0 = (long long)place[b * nblk];
     long long s1 = b + 1 < gridDim.x ? (long long)place[(b + 1) * nblk] : (long long)*total;
     s0 = s0 < 0 ? 0 : (s0 > nnz ? nnz : s0);
     s1 = s1 < s0 ? s0 : (s1 > nnz ? nnz : s1);
     const long long cbase = b << shift;
-    for (int i = threadIdx.x; i < width; i += RANGE_THREADS)
+    for (int i = threadIdx.x; i < counters; i += RANGE_THREADS)
         colcnt[i] = 0;
     __syncthreads();
     for (long long p = s0 + threadIdx.x; p < s1; p += RANGE_THREADS) {
         const long long cl = (long long)cells[p].col - cbase;
-        if (cl >= 0 && cl < width)
-            atomicAdd(&colcnt[cl], 1u);
+        const int g = cells[p].row >> group_shift;
+        if (cl >= 0 && cl < width && g >= 0 && g < groups)
+            atomicAdd(&colcnt[cl * groups + g], 1u);
     }
     __syncthreads();
     unsigned int carry = 0;
-    for (int j0 = 0; j0 < width; j0 += RANGE_THREADS) {
+    for (int j0 = 0; j0 < counters; j0 += RANGE_THREADS) {
         const int j = j0 + threadIdx.x;
-        const unsigned int v = j < width ? colcnt[j] : 0u;
+        const unsigned int v = j < counters ? colcnt[j] : 0u;
         unsigned int tot;
         const unsigned int off = block_exclusive_scan<unsigned int, RANGE_THREADS>(v, &tot) + carry;
-        if (j < width) {
+        if (j < counters) {
             colcnt[j] = off;
-            if (cbase + j < n)
-                tptr[cbase + j] = (RP)(s0 + off);
+            const int c = j / groups;
+            if (j == c * groups && cbase + c < n)
+                tptr[cbase + c] = (RP)(s0 + off);
         }
         carry += tot;
     }
@@ -250,9 +255,10 @@ __global__ void __launch_bounds__(RANGE_THREADS) range_sort_kernel(const Cell *_
     for (long long p = s0 + threadIdx.x; p < s1; p += RANGE_THREADS) {
         const Cell c = cells[p];
         const long long cl = (long long)c.col - cbase;
-        if (cl < 0 || cl >= width)
+        const int g = c.row >> group_shift;
+        if (cl < 0 || cl >= width || g < 0 || g >= groups)
             continue;
-        const long long pos = s0 + (long long)atomicAdd(&colcnt[cl], 1u);
+        const long long pos = s0 + (long long)atomicAdd(&colcnt[cl * groups + g], 1u);
         if (pos < s1) {
             trow[pos] = c.row;
             tval[pos] = c.val;
@@ -294,6 +300,7 @@ inline unsigned grid_for(long long items)
 struct Shape {                   // launch shape of the two-level form
     bool two_level;
     int shift, nranges;
+    int groups, group_shift;     // groups of 2^group_shift rows that the cells of a column are ordered by
     long long rows_per_block, nblk, nhist;
 };
 
@@ -307,6 +314,10 @@ Shape shape_of(long long m, long long n, long long nnz)
     s.two_level = shift <= MAX_RANGE_SHIFT && nnz < 4294967296LL && !(plain && plain[0] == '1');
     s.shift = shift;
     s.nranges = (int)((n + (1LL << shift) - 1) >> shift);
+    const int most = std::max(1, std::min(MAX_GROUPS, RANGE_COUNTERS >> shift));
+    while (((m - 1) >> s.group_shift) >= most)
+        ++s.group_shift;
+    s.groups = (int)((m - 1) >> s.group_shift) + 1;
     // few, large blocks of rows: a block's cells of one range land next to each other (longer runs of writes)
     const long long want = std::max<long long>(1, std::min<long long>(512, (m + 15) / 16));
     s.rows_per_block = (m + want - 1) / want;
@@ -349,8 +360,8 @@ int transpose_typed(const void *rowptr, const int *colidx, const double *vals, l
     scan_apply_kernel<RP><<<(unsigned)nb, SCAN_THREADS, 0, stream>>>(hist, sh.nhist, bsum, (RP *)nullptr, total);
     part_move_kernel<RP, XRP><<<(unsigned)sh.nblk, PART_THREADS, 0, stream>>>((const XRP *)rowptr, colidx, vals, m, n, nnz,
                                                                     sh.rows_per_block, sh.shift, sh.nranges, hist, cells);
-    range_sort_kernel<RP><<<(unsigned)sh.nranges, RANGE_THREADS, (size_t)4 << sh.shift, stream>>>(
-        cells, hist, total, sh.nblk, sh.shift, n, nnz, tptr, trow, tval);
+    range_sort_kernel<RP><<<(unsigned)sh.nranges, RANGE_THREADS, ((size_t)4 << sh.shift) * sh.groups, stream>>>(
+        cells, hist, total, sh.nblk, sh.shift, sh.groups, sh.group_shift, n, nnz, tptr, trow, tval);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -397,6 +408,14 @@ int gather_launch(double *dst, const double *src, const double *perm, long long 
     const long long blocks = (n + 255) / 256;
     gather_kernel<<<(unsigned)(blocks < 8192 ? blocks : 8192), 256, 0, stream>>>(dst, src, perm, n);
     return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+long long transpose_row_grain(long long m, long long n, long long nnz)
+{
+    if (m <= 0 || n <= 0)
+        return 0;
+    const Shape sh = shape_of(m, n, nnz);
+    return sh.two_level ? 1LL << sh.group_shift : 0;
 }
 
 size_t transpose_scratch_bytes(long long m, long long n, long long nnz, int rowptr_is64)

@@ -690,6 +690,53 @@ def _outer_mm_on_all_patterns(agg, rowptr64, left_mm_form):
             assert not got.reshape(-1, r)[empty].any()
 
 
+@pytest.mark.parametrize("r", [33, 64, 100, 101, 128])
+@pytest.mark.parametrize("rowptr64", [False, True])
+def test_outer_row_runs(r, rowptr64, monkeypatch):
+    """The row-run form (a wave per cell, result rows beside U in LDS; forced here with tiny panels) at the edges of its parts:
+    units of 64 cells and more, rows without cells, fewer rows than a block takes, one and two vectors per lane, a side
+    input per cell, values that are not finite, columns that do not ascend, and rows so long that the call falls
+    back to a row per wave.  Sums of at most 700 products of values below 1: 1e-12 of the largest is far above their rounding."""
+    import torch
+    import paper_1801_00829_amd as F
+    monkeypatch.setenv("FUSE_OUTER_PANELS", "2")
+    body = [("uvdot",), ("main",), ("mul",), ("side", 0), ("add",)]
+    rng = np.random.default_rng(5200 + r)
+    F.prepare_outer([("main",), ("uvdot",), ("mul",), ("side", 0), ("mul",)], (60, 60), r, 600, [("colvec", None)], "right_mm", rowptr64)
+    assert "#define FUSE_PANELS 4\n" in F.last_source()         # (a body that no other test compiles)
+    for m, n, d, rb in ((1, 40, 1.0, "0"), (37, 2000, 0.35, "5"), (700, 90, 0.1, "0"), (3000, 33, 0.2, "11"), (50, 9000, 0.01, "64")):
+        rp, ci, va = W.csr_bernoulli(m, n, d, 77)
+        u, v = rng.uniform(size=(m, r)), rng.uniform(size=(n, r))
+        side = rng.uniform(size=(m, 1))
+        x = ops.make_csr(rp, ci, va, (m, n))
+        sides = [("colvec", side)]
+        for limit in ("0", "1"):                     # "1": rows of more than the usual share of a wave go to the other kernel
+            monkeypatch.setenv("FUSE_OUTER_RUNS", "2" if limit == "0" else "1")
+            monkeypatch.setenv("FUSE_OUTER_RB", rb)
+            for agg in ("right_mm", "left_mm") if limit == "0" else ("right_mm",):
+                print("row runs", (m, n, r), agg, "rb", rb, "limit", limit, flush=True)
+                xd = dev_csr(rp, ci, va, (m, n), rowptr64)
+                got = host(F.fuse_outer(body, xd, to_dev(u), to_dev(v), dev_sides(sides), agg))
+                assert_close(got, unfused.outer(body, x, u, v, sides, agg), tol=1e-12, what="row runs %s" % agg)
+                if agg == "right_mm":
+                    assert np.array_equal(got, host(F.fuse_outer(body, xd, to_dev(u), to_dev(v), dev_sides(sides), agg)))
+        for agg in ("full", "none"):                 # the sums and values of the same traversal
+            monkeypatch.setenv("FUSE_OUTER_RUNS", "2")
+            got = host(F.fuse_outer(body, dev_csr(rp, ci, va, (m, n), rowptr64), to_dev(u), to_dev(v), dev_sides(sides), agg))
+            assert_close(got, unfused.outer(body, x, u, v, sides, agg), tol=1e-12, what="row runs %s" % agg)
+        # columns in any order
+        perm = np.concatenate([rp[i] + rng.permutation(rp[i + 1] - rp[i]) for i in range(m)]).astype(np.int64) if va.size else np.zeros(0, np.int64)
+        got = host(F.fuse_outer(ALS_W, dev_csr(rp, ci[perm], va[perm], (m, n), rowptr64), to_dev(u), to_dev(v), [], "right_mm"))
+        assert_close(got, unfused.outer(ALS_W, x, u, v, [], "right_mm"), tol=1e-12, what="row runs, any order")
+        # an infinite row of V reaches the rows with a cell in its column and no other
+        v2 = v.copy()
+        v2[n // 2] = np.inf
+        got = host(F.fuse_outer(ALS_W, dev_csr(rp, ci, va, (m, n), rowptr64), to_dev(u), to_dev(v2), [], "right_mm")).reshape(m, r)
+        hit = np.zeros(m, bool)
+        hit[np.repeat(np.arange(m), np.diff(rp))[ci == n // 2]] = True
+        assert np.isinf(got[hit]).all() and np.isfinite(got[~hit]).all()
+
+
 def test_outer_right_mm_on_all_patterns():
     _outer_mm_on_all_patterns("right_mm", False, "")
 
