@@ -472,26 +472,34 @@ int row_mfma_impl(const Program &prog, const std::string &pkey, const fuse_dense
         const double avg = m > 0 ? (double)Xs->nnz / (double)m : 1.0;
         return (int)std::min<int64_t>(16, std::max<int64_t>(1, (int64_t)(avg * 1.34 / threads) + 1));
     };
-    // Pipelined form (FUSE_MFMA_PIPE: 0 never, 1 by the rules here and below, 2 wherever a tile fits): 7 product waves and one for the generated code, one block per CU; the most
+    // Pipelined form (FUSE_MFMA_PIPE: 0 never, 1 by the rules here and below, 2 wherever a tile fits, 3 for CSR input of any width too): 7 product waves (11 for CSR
+    // input, whose tiles travel in few registers) and one for the generated code, one block per CU; the most
     // rows per tile of which four tiles fit in LDS, while V, the running sums and two travelling tiles leave a thread 60 of
-    // its 256 registers.  2.4 GB, logistic regression core, block form / pipelined: n = 128 k = 4 586 / 564, k = 16
+    // its 256 (168) registers.  2.4 GB, logistic regression core, block form / pipelined: n = 128 k = 4 586 / 564, k = 16
     // 1285 / 1015 us; n = 256 460 / 466, 818 / 814; n = 500 540 / 438, 718 / 674; n = 784 494 / 436, 832 / 660; n = 1000
     // 492 / 429, 1542 / 665; 1.6 GB, strided rows: n = 16 k = 8 2725 / 1986, k = 16 2904 / 2955, n = 64 k = 8 753 / 633, n = 100
-    // k = 4 523 / 353, k = 16 1017 / 730.  CSR rows are scattered by as many waves as a tile has rows, so a tile of 4 gains nothing (784
-    // columns, a quarter stored, k = 10: 1472 / 1490 us) and few columns are cheaper in the block form (112 columns, 30 %
-    // stored, k = 10: 887 / 1048; 300 columns, 20 %, log-normal rows, k = 5 / 10: 2033 / 1395, 2070 / 1518; 500 columns, 16 %, k = 5 / 10 / 16:
-    // 1048 / 867, 1075 / 996, 1106 / 1150).
+    // k = 4 523 / 353, k = 16 1017 / 730.  CSR, 4e7 cells, a quarter stored, k = 5 / 10 / 16: n = 150 423 / 398, 683 / 498, 763 /
+    // 582; 200 378 / 356, 565 / 469, 615 / 543; 300 442 / 298, 456 / 354, 473 / 421; 500 349 / 248, 355 / 304; 784 306 / 225,
+    // 310 / 265, 322 / 319; 900 303 / 227, 325 / 281, 605 / 340; 1050 477 / 215, 453 / 262, 664 / 318; but 112 columns k = 10 524 /
+    // 556, 250 columns k = 5 / 8 321 / 336, 324 / 337, and where 13 classes and more halve the tile 500 columns 373 / 396, 650
+    // 331 / 362.  With log-normal rows 4e7 cells, 15 % stored, k = 10: n = 300 1281 / 566, 500 1064 / 481, 784 1097 / 462.
     int TR = 16;
     bool pipe = false;
-    const int ns_ = std::max(nsides, 1), mp = (kd + 3) / 4, NPROD = 7;
+    const int ns_ = std::max(nsides, 1), mp = (kd + 3) / 4, NPROD = Xs ? 11 : 7;
     const int64_t np_pipe = nct * 16 + (40 - nct * 16 % 32) % 32;          // 8 modulo 32
     const int pipe_mode = env_int("FUSE_MFMA_PIPE", 1);
-    if (pipe_mode != 0 && (!Xs || (Xs->nnz > 0 && n >= 256 && kd <= 12))) {
-        for (int tr = Xs ? 8 : 16; tr >= (Xs ? 8 : 4) && !pipe; tr >>= 1) {
+    // cells per thread of the pipelined form: four standard deviations above a tile's mean
+    auto tile_cap = [&](int tr) {
+        const double avg = m > 0 ? (double)Xs->nnz / (double)m * tr : 1.0;
+        return (int)std::min<double>(16.0, std::ceil((avg + 4.0 * std::sqrt(avg)) / (64.0 * NPROD)));
+    };
+    const bool csr_pipe = Xs && Xs->nnz > 0 && (pipe_mode == 3 || (pipe_mode == 2 && n >= 256 && n <= 560 && kd <= 12) || (pipe_mode == 1 && n >= 128 && !(nct == 16 && kd <= 8) && !(kd > 12 && n > 480 && n <= 704)));
+    if (pipe_mode != 0 && (!Xs || csr_pipe)) {
+        for (int tr = 16; tr >= 4 && !pipe; tr >>= 1) {
             const int64_t lds = (4 * tr * np_pipe + (int64_t)(2 * NPROD + 3 + ns_) * tr * (4 * mp + 1)) * 8;
             const int64_t held = (nct + NPROD - 1) / NPROD * mp * 4;
-            const int64_t travel = Xs ? (tr + NPROD - 1) / NPROD * (3 * csr_cap(64) + 4) : (nvec + 64 * NPROD / tr - 1) / (64 * NPROD / tr) * VEC * 2;
-            if (lds <= 158 * 1024 && held + 2 * travel <= 196) {
+            const int64_t travel = Xs ? 3 * tile_cap(tr) + 2 : (nvec + 64 * NPROD / tr - 1) / (64 * NPROD / tr) * VEC * 2;
+            if (lds <= 158 * 1024 && held + 2 * travel <= (NPROD > 7 ? 112 : 196)) {
                 pipe = true;
                 TR = tr;
             }
@@ -529,9 +537,9 @@ int row_mfma_impl(const Program &prog, const std::string &pkey, const fuse_dense
     int m4 = env_int("FUSE_MFMA_M4", -1);
     if (m4 != 0 && m4 != 1)
         m4 = kd <= 4 ? 1 : 0;
-    const int cap = !Xs ? 1 : csr_cap(pipe ? 64 : BLOCK / 16);
+    const int cap = !Xs ? 1 : pipe ? tile_cap(TR) : csr_cap(BLOCK / 16);
     const std::string key = std::string(pipe ? "rowmfmap|" : "rowmfma|") + pkey + "|" + side_key(sides, nsides) + "|v" + std::to_string(VEC) +
-                            "n" + std::to_string(nct) + (pipe ? "r" + std::to_string(TR) + "l" + std::to_string(nld) : "w" + std::to_string(NWAVE)) + "nt" + std::to_string(env_int("FUSE_NT", 1)) +
+                            "n" + std::to_string(nct) + (pipe ? "w" + std::to_string(NPROD) + "r" + std::to_string(TR) + "l" + std::to_string(nld) : "w" + std::to_string(NWAVE)) + "nt" + std::to_string(env_int("FUSE_NT", 1)) +
                             (pipe ? "" : "m" + std::to_string(m4)) + (csrx ? "csr" + std::to_string(rp64) + "c" + std::to_string(cap) : "");
     std::shared_ptr<Plan> plan;
     int rc = rt.plan(key, pipe ? "fuse_row_mfma_pipe" : "fuse_row_mfma", [&](const std::string &name) {
@@ -539,7 +547,7 @@ int row_mfma_impl(const Program &prog, const std::string &pkey, const fuse_dense
         s += "#define FUSE_NT " + std::to_string(env_int("FUSE_NT", 1)) + "\n";
         s += kSrcCommon;
         s += "#define FUSE_KERNEL_NAME " + name + "\n";
-        s += pipe ? "#define FUSE_TR " + std::to_string(TR) + "\n#define FUSE_RPW " + std::to_string((TR + NPROD - 1) / NPROD) + "\n"
+        s += pipe ? "#define FUSE_TR " + std::to_string(TR) + "\n"
                   : "#define FUSE_M4 " + std::to_string(m4) + "\n";
         s += "#define FUSE_CSRX " + std::to_string(csrx) + "\n#define FUSE_RP64 " + std::to_string(rp64) + "\n#define FUSE_CAP " +
              std::to_string(cap) + "\n";
@@ -642,7 +650,7 @@ int row_dense_impl(const Program &prog, const std::string &pkey, const fuse_dens
         //  10.4, x 256 11.1 / 12.8, x 400 18.2 / 14.0, 8000 x 256 15.1 / 13.0
         int min_k = env_int("FUSE_MFMA_MIN_K", -1);
         const int pipe_mode = env_int("FUSE_MFMA_PIPE", 1);          // (three classes are for the pipelined form only)
-        const bool pipe3 = n >= 120 && pipe_mode != 0 && (pipe_mode == 2 || n >= 384 || m >= 24 * (int64_t)rt.num_cus());
+        const bool pipe3 = n >= 120 && pipe_mode != 0 && (pipe_mode >= 2 || n >= 384 || m >= 24 * (int64_t)rt.num_cus());
         if (min_k < 0)
             min_k = !mfma_wave_form(X, launch) ? (pipe3 ? 3 : 4) : n >= 48 ? 2 : n > 16 ? 3 : 4;
         const int64_t tile_bytes = (16 * ((n + 15) / 16 * 16 + 1) + (int64_t)(4 + 2 + std::max(nsides, 1)) * 272 + 128) * 8;
@@ -994,22 +1002,26 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
     const int64_t nacck = rk == KIND_VK ? kd : 1;           // running sums per column
 
     // t(X) %*% f(X %*% V) over a matrix that stores a good part of its cells (Mnist-like: a quarter): the dense
-    // matrix-unit form, whose LDS tile is filled from the CSR rows; its time does not depend on the density, the
-    // lane-group form's is proportional to it (FUSE_MFMA_CSR_DENSITY: least stored share in percent, default 15;
-    // FUSE_MFMA_CSR_MIN_K: least number of classes, default 5, 0 = never).  8e7 cells, logistic regression core, lane groups /
-    // block form / pipelined form: 112 columns, 30 % stored, k = 5 540 / 838 / -, k = 6 636 / 845, k = 8 1418 / 859, k = 10
-    // 2139 / 881; 15 %, k = 5 549 / 1572, k = 8 1428 / 1633, k = 10 2185 / 1695; 300 columns, 20 %, k = 5 602 / 1108 / 939, k = 6
-    // 693 / 1122 / 956, k = 8 1518 / 1120 / 953; 500 columns, 16 %, k = 5 520 / 1046 / 872, k = 8 1440 / 1062 / 874; 25 %, k = 5
-    // 633 / 703 / 531; 560 columns, 30 %, k = 5 569 / 589 / 455; 784 columns, 15 %, k = 5 771 / 954, k = 6 814 / 963, k = 8 1695 /
-    // 998; 25 %, k = 5 630 / 616.  So with 5 and 6 classes the lane groups are up to three times faster where less than about a
-    // quarter is stored: the line at 5 classes is right for a quarter and more only.
+    // matrix-unit forms, whose LDS tile is filled from the CSR rows; their time goes by rows x columns, the lane-group form's by
+    // stored cells (FUSE_MFMA_CSR_MIN_K: least number of classes, default 5, 0 = never; FUSE_MFMA_CSR_DENSITY: least stored
+    // share in percent instead of the estimate).  From 7 classes and 15 % on always: lane groups wait for the longest of their
+    // rows, which the host does not know.  Elsewhere by an estimate in picoseconds per cell, after: lane groups, 4e7 cells, k = 5 / 8 /
+    // 10 / 14 / 16, n = 300 258 / 734 / 1068 / 2811 / 3552 us, 500 320 / 839 / 1380 / 3162 / 3962, 900 324 / 743 / 1155 / 2376 / 2957;
+    // matrix units, 1.6e8 cells of dense tiles, n = 64 719 / - / 760 / 930, 112 451 / 452 / 524 / 660 / 655, 200 356 / 360 / 469 /
+    // 538 / 543, 300 298 / 300 / 354 / 416 / 421, 500 248 / 252 / 304 / 367 / 373, 900 227 / 232 / 281 / 326 / 340.  Near the line, lane groups /
+    // matrix units: 300 columns, 15 % stored, k = 5 226 / 474, 25 % 258 / 298; 500 columns k = 5 15 % 274 / 375, 25 % 320 / 248; 784
+    // columns k = 5 15 % 384 / 354; k = 10, 8 % stored: n = 300 491 / 514, 500 572 / 420, 784 669 / 403.
     {
         int vside = -1;
         const int min_k = env_int("FUSE_MFMA_CSR_MIN_K", 5);
-        const double share = (m > 0 && n > 0) ? 100.0 * (double)X->nnz / ((double)m * (double)n) : 0.0;
+        const double share = (m > 0 && n > 0) ? (double)X->nnz / ((double)m * (double)n) : 0.0;
+        const int least = env_int("FUSE_MFMA_CSR_DENSITY", -1);
+        static const double lane_ps[FUSE_MAX_K + 1] = {1, 1, 2, 3, 5, 7, 7.7, 10, 18, 23, 30, 33, 36, 65, 85, 90, 100};
+        const double lanes = lane_ps[std::min(std::max(kd, 0), FUSE_MAX_K)] * (n < 400 ? 0.85 : 1.1);
+        const double tiles = (n < 100 ? 4.5 : n < 128 ? 2.9 : n < 256 ? 2.35 : n < 400 ? 1.87 : 1.5) * (kd <= 8 ? 1.0 : kd <= 12 ? 1.2 : 1.4);
+        const bool pays = least >= 0 ? 100.0 * share >= (double)least : (share >= 0.15 && kd >= 7) || share * lanes >= tiles;
         const int64_t tile_bytes = (16 * ((n + 15) / 16 * 16 + 1) + (int64_t)(4 + 2 + std::max(nsides, 1)) * 272 + 128) * 8;
-        if (ac == 3 && min_k > 0 && kd >= min_k && n >= 16 && tile_bytes <= 158 * 1024 &&
-            share >= (double)env_int("FUSE_MFMA_CSR_DENSITY", 15) && mfma_pattern(prog, sides, nsides, vside))
+        if (ac == 3 && min_k > 0 && kd >= min_k && n >= 16 && tile_bytes <= 158 * 1024 && pays && mfma_pattern(prog, sides, nsides, vside))
             return row_mfma_impl(prog, prog.key, nullptr, X, sides, nsides, vside, out, stream, launch);
     }
 

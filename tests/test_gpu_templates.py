@@ -1290,6 +1290,37 @@ def test_row_csr_matrix_rhs_through_the_matrix_units(case, rowptr64, monkeypatch
         assert_close(got, other, scale=fac * scale, what="csr matrix units against lane groups")
 
 
+@pytest.mark.parametrize("n,k", [(128, 13), (129, 9), (256, 12), (500, 14), (640, 8), (650, 8), (656, 16), (680, 8), (784, 10), (1101, 5)])
+@pytest.mark.parametrize("rowptr64", [False, True])
+def test_row_csr_matrix_units_pipelined(n, k, rowptr64, monkeypatch):
+    """The pipelined matrix-unit form over CSR rows: tiles of 16, 8 and 4 rows, column tiles that do not divide by the waves,
+    rows so long that their tile has more cells than travel in registers, rows without cells, a last tile that is not full;
+    enough rows that a block gets several tiles, so that every buffer is cleared and filled again.  The bound of the tests around
+    it: 1e-10 of the condition-aware scale."""
+    import paper_1801_00829_amd as F
+    monkeypatch.setenv("FUSE_MFMA_PIPE", "3")
+    monkeypatch.setenv("FUSE_MFMA_CSR_DENSITY", "1")
+    m = 256 * 16 * 3 + 5
+    rng = np.random.default_rng(n + k)
+    lens = rng.binomial(n, 0.04, m)
+    lens[::7] = 0
+    lens[100:140] = n                               # ten and more full tiles, far beyond what travels
+    lens[-1] = n // 2
+    rp = np.zeros(m + 1, np.int64)
+    np.cumsum(lens, out=rp[1:])
+    ci = np.concatenate([np.sort(rng.permutation(n)[:c]) for c in lens]).astype(np.int32)
+    va = rng.uniform(0.1, 1.0, rp[-1])
+    x = ops.make_csr(rp, ci, va, (m, n))
+    v, p = rng.normal(size=(n, k)), rng.uniform(size=(m, k))
+    hs = [("rhs", v), ("kvec", p)]
+    absq = ops.csr_matmul_dense(x, x.vals, np.abs(v))
+    scale = max(ops.csr_t_matmul_dense(x, x.vals, absq).max(initial=0.0), 1e-300)
+    print("csr pipelined", (m, n, k), "rowptr64", rowptr64, flush=True)
+    got = host(F.fuse_row(MLOGREG, dev_csr(rp, ci, va, (m, n), rowptr64), [("rhs", to_dev(v)), ("kvec", to_dev(p))], "col_t")).reshape(n, k)
+    assert F.last_kernel().startswith("fuse_row_mfma_pipe_")
+    assert_close(got, unfused.row_csr(MLOGREG, x, hs, "col_t"), scale=2.0 * k * scale, what="csr pipelined")
+
+
 def test_row_matrix_rhs_strided_sides_and_limits(rhs_form):
     import paper_1801_00829_amd as F
     from oracle import plans
