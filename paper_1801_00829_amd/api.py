@@ -2,6 +2,8 @@
 import ctypes
 from collections import namedtuple
 
+import torch
+
 from . import _lib as L
 
 AGG = {"none": 0, "full": 1, "row": 2, "col": 3, "col_t": 4, "right_mm": 5, "left_mm": 6}
@@ -42,12 +44,18 @@ def _expr(tokens):
     Marshalled descriptors are kept by value of the list, so a loop that issues the same
     operator again does not rebuild the token array."""
     try:
+        hit = _EXPR_CACHE.get(tuple(tokens))
+        if hit is not None:
+            return hit
         key = tuple(tuple(t) for t in tokens)
-        hit = _EXPR_CACHE.get(key)
-    except TypeError:                      # unhashable token entries: marshal without caching
-        key, hit = None, None
-    if hit is not None:
-        return hit
+    except TypeError:                      # tokens given as lists, or with unhashable entries
+        try:
+            key = tuple(tuple(t) for t in tokens)
+            hit = _EXPR_CACHE.get(key)
+        except TypeError:                  # marshal without caching
+            key, hit = None, None
+        if hit is not None:
+            return hit
     arr = (L.Tok * max(len(tokens), 1))()
     for i, t in enumerate(tokens):
         name = t[0]
@@ -73,7 +81,6 @@ def _on_gpu(t, what):
 
 def _dense(t, rows=None, cols=None):
     """2-D (or 1-D) float64 tensor with unit column stride -> Dense descriptor."""
-    import torch
     if t is None:
         return None
     if isinstance(t, tuple):                      # shape only (prepare_*): (rows, cols[, ld])
@@ -84,44 +91,47 @@ def _dense(t, rows=None, cols=None):
     _on_gpu(t, "matrix")
     if t.dim() == 1:
         t = t.view(-1, 1) if cols == 1 else t.view(1, -1)
-    if t.dim() != 2 or (t.shape[1] > 1 and t.stride(1) != 1):
+    shape = t.shape
+    if len(shape) != 2:
         raise ValueError("need a 2-D tensor with unit column stride")
-    ld = t.stride(0) if t.shape[0] > 1 else max(t.shape[1], 1)
-    if t.shape[1] == 1 and t.shape[0] > 1:
-        ld = t.stride(0)
-    return L.Dense(t.data_ptr(), t.shape[0], t.shape[1], max(int(ld), 1))
+    r, c = shape
+    sr, sc = t.stride()
+    if c > 1 and sc != 1:
+        raise ValueError("need a 2-D tensor with unit column stride")
+    ld = sr if r > 1 else max(c, 1)
+    return L.Dense(t.data_ptr(), r, c, ld if ld > 1 else 1)
 
 
 def _sides(sides, m, n):
     """[(kind, tensor | float | shape-tuple)] -> (Side array, count)."""
-    import torch
     arr = (L.Side * max(len(sides), 1))()
     arr._keep = []                                        # CSR descriptors of sparse sides live as long as the array
     for k, (kind, val) in enumerate(sides):
-        arr[k].kind = SIDE[kind]
+        a = arr[k]
+        a.kind = SIDE[kind]
         if kind == "scalar":
-            arr[k].scalar = float(val)
+            a.scalar = float(val)
         elif kind == "sparse":                            # a Csr of device tensors, or prepare_*: (is64, None, nnz, shape)
             desc = _csr(val)
             arr._keep.append(desc)
-            arr[k].sp = ctypes.pointer(desc)
+            a.sp = ctypes.pointer(desc)
         elif kind in ("rhs", "kvec"):
             if isinstance(val, tuple):                    # shape only: (rows, k)
-                arr[k].m = L.Dense(None, int(val[0]), int(val[1]), int(val[1]))
+                a.m = L.Dense(None, int(val[0]), int(val[1]), int(val[1]))
             else:
-                arr[k].m = _dense(val)
+                a.m = _dense(val)
         elif kind == "colvec":
             if isinstance(val, tuple) or val is None:
-                arr[k].m = L.Dense(None, m, 1, 1)
+                a.m = L.Dense(None, m, 1, 1)
             else:
                 v = val.view(-1, 1) if val.dim() == 1 else val
                 if v.dtype != torch.float64:
                     raise TypeError("libfuse vectors are float64")
                 _on_gpu(v, "column-vector side")
-                arr[k].m = L.Dense(v.data_ptr(), v.shape[0], 1, max(int(v.stride(0)), 1))
+                a.m = L.Dense(v.data_ptr(), v.shape[0], 1, max(int(v.stride(0)), 1))
         elif kind == "rowvec":
             if isinstance(val, tuple) or val is None:
-                arr[k].m = L.Dense(None, 1, n, max(n, 1))
+                a.m = L.Dense(None, 1, n, max(n, 1))
             else:
                 v = val.reshape(1, -1) if val.dim() == 1 else val
                 if v.dtype != torch.float64:
@@ -133,14 +143,13 @@ def _sides(sides, m, n):
                     v = v.view(1, -1)
                 if v.shape[1] > 1 and v.stride(1) != 1:
                     raise ValueError("row-vector side must be contiguous")
-                arr[k].m = L.Dense(v.data_ptr(), 1, v.shape[1], max(v.shape[1], 1))
+                a.m = L.Dense(v.data_ptr(), 1, v.shape[1], max(v.shape[1], 1))
         else:
-            arr[k].m = _dense(val if val is not None else (m, n))
+            a.m = _dense(val if val is not None else (m, n))
     return arr, len(sides)
 
 
 def _csr(x):
-    import torch
     rowptr, colidx, vals, shape = x
     m, n = int(shape[0]), int(shape[1])
     if isinstance(rowptr, int):                   # prepare_*: (is64, None, nnz, shape)
@@ -160,14 +169,15 @@ def _csr(x):
 
 
 def _stream(stream):
-    import torch
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # the current stream of the current device, without an object for it.  (Small operators are bound by this module: cell over
+        # 100 x 100 14.2 us per call with a stream object, a descriptor key built token by token and each tensor's shape and
+        # strides asked for several times, 9.5 us now; row 17.6 and 14.7 with the library's result count kept by value.)
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
     return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
 
 
 def _out(out, count, like):
-    import torch
     if out is None:
         out = torch.empty(int(count), dtype=torch.float64, device=like.device)
     elif out.dtype != torch.float64 or not out.is_contiguous() or out.numel() < count or not out.is_cuda:
@@ -274,6 +284,28 @@ def _row_out_count(lib, e, xd, xs, sa, ns, agg):
     return cnt.value
 
 
+_ROW_COUNTS = {}
+_ROW_COUNT_KINDS = frozenset(("matrix", "colvec", "rowvec", "scalar"))
+
+
+def _row_count(lib, e, expr, xd, xs, sides, sa, ns, agg):
+    """_row_out_count, kept by value of what it depends on (sides without a shape of their own: their kinds)."""
+    kinds = tuple([s[0] for s in sides])
+    if not _ROW_COUNT_KINDS.issuperset(kinds):
+        return _row_out_count(lib, e, xd, xs, sa, ns, agg)
+    try:
+        key = (tuple(expr), kinds, agg, xd.rows, xd.cols, -1) if xs is None else (tuple(expr), kinds, agg, xs.rows, xs.cols, xs.nnz)
+        count = _ROW_COUNTS.get(key)
+    except TypeError:                      # tokens given as lists
+        return _row_out_count(lib, e, xd, xs, sa, ns, agg)
+    if count is None:
+        count = _row_out_count(lib, e, xd, xs, sa, ns, agg)
+        if len(_ROW_COUNTS) > 1024:
+            _ROW_COUNTS.clear()
+        _ROW_COUNTS[key] = count
+    return count
+
+
 def fuse_row(expr, X, sides=(), agg="col_t", out=None, stream=None):
     """C: fuse_row.  X: cuda float64 (m, n) tensor or a Csr of device tensors."""
     lib = L.load()
@@ -283,13 +315,13 @@ def fuse_row(expr, X, sides=(), agg="col_t", out=None, stream=None):
         xs = _csr(X)
         m, n = xs.rows, xs.cols
         sa, ns = _sides(sides, m, n)
-        out = _out(out, _row_out_count(lib, e, None, xs, sa, ns, agg), X.vals)
+        out = _out(out, _row_count(lib, e, expr, None, xs, sides, sa, ns, agg), X.vals)
         _check(lib.fuse_row(ctypes.byref(e), None, ctypes.byref(xs), sa, ns, AGG[agg], out.data_ptr(),
                             _stream(stream)))
     else:
         xd = _dense(X)
         sa, ns = _sides(sides, xd.rows, xd.cols)
-        out = _out(out, _row_out_count(lib, e, xd, None, sa, ns, agg), X)
+        out = _out(out, _row_count(lib, e, expr, xd, None, sides, sa, ns, agg), X)
         _check(lib.fuse_row(ctypes.byref(e), ctypes.byref(xd), None, sa, ns, AGG[agg], out.data_ptr(),
                             _stream(stream)))
     return out
@@ -312,7 +344,6 @@ def fuse_outer(expr, X, U, V, sides=(), agg="full", out=None, stream=None):
 def outer_left_prepare(X, stream=None):
     """C: fuse_outer_left_pattern_bytes + fuse_outer_left_prepare.  Returns the prepared pattern of X (a uint8
     device tensor that the caller keeps for as long as it calls fuse_outer_left with it)."""
-    import torch
     lib = L.load()
     xs = _csr(X)
     nbytes = int(lib.fuse_outer_left_pattern_bytes(ctypes.byref(xs)))
@@ -438,7 +469,6 @@ def probe_read(src, sink, blocks, stream=None, n_doubles=None):
 
 def probe_gather(table, idx, sink, blocks, stream=None):
     """C: fuse_probe_gather.  table: cuda float64 (rows, row_doubles); idx: cuda int32 row numbers."""
-    import torch
     if table.dtype != torch.float64 or idx.dtype != torch.int32 or table.dim() != 2 or table.stride(1) != 1:
         raise TypeError("probe_gather needs a float64 table with unit column stride and int32 indices")
     for t_, what in ((table, "table"), (idx, "idx"), (sink, "sink")):
