@@ -314,7 +314,11 @@ Shape shape_of(long long m, long long n, long long nnz)
     s.two_level = shift <= MAX_RANGE_SHIFT && nnz < 4294967296LL && !(plain && plain[0] == '1');
     s.shift = shift;
     s.nranges = (int)((n + (1LL << shift) - 1) >> shift);
-    const int most = std::max(1, std::min(MAX_GROUPS, RANGE_COUNTERS >> shift));
+    // (groups only where a product would walk panels of the result: 1.5 million cells and 12 MB of rows of at most 128 columns;
+    // they cost a small matrix 70 us of preparation.  FUSE_OUTER_PANELS=2: panels on small inputs)
+    const char *panels = std::getenv("FUSE_OUTER_PANELS");
+    const bool grouped = (nnz >= 1500000 && m * 1024 > (12LL << 20)) || (panels && panels[0] == '2');
+    const int most = grouped ? std::max(1, std::min(MAX_GROUPS, RANGE_COUNTERS >> shift)) : 1;
     while (((m - 1) >> s.group_shift) >= most)
         ++s.group_shift;
     s.groups = (int)((m - 1) >> s.group_shift) + 1;
