@@ -737,6 +737,27 @@ def test_outer_row_runs(r, rowptr64, monkeypatch):
         assert np.isinf(got[hit]).all() and np.isfinite(got[~hit]).all()
 
 
+@pytest.mark.parametrize("kind", ["matrix", "rowvec"])
+@pytest.mark.parametrize("agg", ["right_mm", "left_mm"])
+def test_outer_row_runs_side_inputs_by_column(kind, agg, monkeypatch):
+    """Side inputs addressed by the cell's column in the row-run form, with blocks that have no rows (37 and 300 rows, 5 and 2
+    per block of a CU).  Tolerance as above."""
+    import paper_1801_00829_amd as F
+    monkeypatch.setenv("FUSE_OUTER_PANELS", "2")
+    monkeypatch.setenv("FUSE_OUTER_RUNS", "2")
+    body = [("uvdot",), ("main",), ("mul",), ("side", 0), ("add",)]
+    rng = np.random.default_rng(5300)
+    r = 100
+    for m, n, d, rb in ((37, 2000, 0.35, "5"), (300, 90, 0.3, "2")):
+        monkeypatch.setenv("FUSE_OUTER_RB", rb)
+        rp, ci, va = W.csr_bernoulli(m, n, d, 78)
+        u, v = rng.uniform(size=(m, r)), rng.uniform(size=(n, r))
+        sides = [(kind, rng.uniform(size=(m, n) if kind == "matrix" else (1, n)))]
+        print("row runs", (m, n, r), kind, agg, flush=True)
+        got = host(F.fuse_outer(body, dev_csr(rp, ci, va, (m, n), False), to_dev(u), to_dev(v), dev_sides(sides), agg))
+        assert_close(got, unfused.outer(body, ops.make_csr(rp, ci, va, (m, n)), u, v, sides, agg), tol=1e-12, what="row runs, %s" % kind)
+
+
 def test_outer_right_mm_on_all_patterns():
     _outer_mm_on_all_patterns("right_mm", False, "")
 

@@ -1,0 +1,80 @@
+"""Generated kernels run on the CPU, every access checked against the ends of its buffers, against the oracle."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from emu_util import Args, Kernels
+from oracle import ops, unfused
+
+
+@pytest.fixture(scope="module")
+def F():
+    import paper_1801_00829_amd as F
+    from paper_1801_00829_amd import build as B
+    if B.needs_build():
+        B.build()
+    return F
+
+
+def _ptr(a):
+    return a.ctypes.data
+
+
+# ------------------------------------------------------------------ outer products, row runs --
+
+def _run_row_runs(F, folder, monkeypatch, body, kind, transposed, r, rb, blocks, mask, rp64=False, width=3, last_first=False):
+    """RIGHT_MM over the cells that `mask` (m x n) has, with one side input of that kind: through the preparatory kernel, the main
+    one with `blocks` blocks, and the one for long rows.  transposed: the kernels' LEFT_MM build, over the transposed matrix.  Returns
+    (result, oracle)."""
+    monkeypatch.setenv("FUSE_OUTER_PANELS", "2")
+    monkeypatch.setenv("FUSE_OUTER_RUNS", "2")
+    monkeypatch.setenv("FUSE_OUTER_RB", str(rb))
+    m, n = mask.shape
+    rng = np.random.default_rng(17 + m + n + r)
+    rp, ci = np.concatenate([[0], np.cumsum(mask.sum(1))]), np.nonzero(mask)[1].astype(np.int32)
+    va = rng.uniform(0.1, 1.0, len(ci))
+    x = ops.make_csr(rp, ci, va, (m, n))
+    u, v = rng.uniform(size=(m, r)), rng.uniform(size=(n, r))
+    side = rng.uniform(size={"matrix": (m, n), "colvec": (m, 1), "rowvec": (1, n)}[kind])
+    agg = "left_mm" if transposed else "right_mm"
+    F.prepare_outer(body, (m, n), r, max(len(ci), 1), [(kind, None)], agg, rp64)
+    name = F.last_kernel()
+    k = Kernels(F.last_source(), folder, [name, "fuse_outer_prep", "fuse_outer_rows"])
+    assert k.define("FUSE_PANELS") == 4 and k.define("FUSE_TRANSPOSED") == int(transposed)
+    if transposed:                                  # the walked matrix: the columns of X, factors exchanged
+        order = np.argsort(ci, kind="stable")
+        rows = np.repeat(np.arange(m), np.diff(rp))
+        wrp = np.concatenate([[0], np.cumsum(np.bincount(ci, minlength=n))])
+        wci, wva, wm, wn, wu, wv = rows[order], va[order], n, m, v, u
+    else:
+        wrp, wci, wva, wm, wn, wu, wv = rp, ci, va, m, n, u, v
+    a = Args()
+    keep = dict(x=k.copy(wva, np.float64), colidx=k.copy(wci, np.int32), rowptr=k.copy(wrp, np.int64 if rp64 else np.int32), u=k.copy(wu), v=k.copy(wv),
+                out=k.copy(np.full((wm, r), np.nan)), ticket=k.buffer(64, np.uint32), partials=k.buffer(64))
+    for f, b in keep.items():
+        setattr(a, f, _ptr(b))
+    s = k.copy(side)
+    a.side[0], a.side_ld[0] = _ptr(s), s.shape[1]
+    a.ldu = a.ldv = a.rank = r
+    a.m, a.n, a.nnz = wm, wn, len(wci)
+    P = (wn + width - 1) // width
+    pp = k.buffer((wm, P + 1), np.int64 if rp64 else np.int32)
+    a.npanels, a.panel_w, a.panel_ptr = P, width, _ptr(pp)
+    a.long_rows = _ptr(keep["ticket"]) + 128
+    a.row_limit = len(wci)
+    k.run("fuse_outer_prep", a, (wm * 16 + 255) // 256, 256, last_first)
+    k.run(name, a, blocks, k.define("FUSE_BLOCK"), last_first)
+    k.run("fuse_outer_rows", a, 2, 256, last_first)
+    return keep["out"].copy(), unfused.outer(body, x, u, v, [(kind, side)], agg)
+
+
+@pytest.mark.parametrize("kind,transposed", [("matrix", False), ("colvec", False), ("matrix", True), ("rowvec", True)])
+def test_row_runs_read_side_inputs_of_existing_cells_only(F, tmp_path, monkeypatch, kind, transposed):
+    """More blocks than the rows fill: 11 rows, 4 per block, 5 blocks, of which the last two have none."""
+    mask = np.random.default_rng(3).uniform(size=(2, 11) if transposed else (11, 9)) < 0.6
+    if transposed:
+        mask[:, 0] = False, True                    # the walked matrix' first cell lies in the last row of the side
+    body = [("uvdot",), ("main",), ("mul",), ("side", 0), ("add",)]
+    got, want = _run_row_runs(F, tmp_path, monkeypatch, body, kind, transposed, 33, 4, 5, mask, width=1 if transposed else 3)
+    assert np.abs(got - want.reshape(got.shape)).max() <= 1e-12 * np.abs(want).max()
