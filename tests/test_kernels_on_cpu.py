@@ -78,3 +78,46 @@ def test_row_runs_read_side_inputs_of_existing_cells_only(F, tmp_path, monkeypat
     body = [("uvdot",), ("main",), ("mul",), ("side", 0), ("add",)]
     got, want = _run_row_runs(F, tmp_path, monkeypatch, body, kind, transposed, 33, 4, 5, mask, width=1 if transposed else 3)
     assert np.abs(got - want.reshape(got.shape)).max() <= 1e-12 * np.abs(want).max()
+
+
+# --------------------------------------------------- matrix units over CSR rows, pipelined form --
+
+_Q = [("side", 1), ("main",), ("side", 0), ("matmult",), ("mul",)]
+MLOGREG = [("main",)] + _Q + [("side", 1)] + _Q + [("rowsum",), ("mul",), ("sub",), ("outerk",)]
+
+
+def _run_csr_pipe(F, folder, monkeypatch, mask, k, rp64=False, before=0, blocks=2, change=None, last_first=False):
+    """t(X) %*% f(X %*% V) over the cells that `mask` has, in CSR arrays that hold `before` cells in front of them.
+    Returns (result, X, V, P)."""
+    monkeypatch.setenv("FUSE_MFMA_PIPE", "3")
+    monkeypatch.setenv("FUSE_MFMA_CSR_DENSITY", "1")
+    m, n = mask.shape
+    rng = np.random.default_rng(n + k)
+    rp = before + np.concatenate([[0], np.cumsum(mask.sum(1))])
+    ci = np.nonzero(mask)[1]
+    vals = {"x": rng.uniform(0.1, 1.0, len(ci)), "v": rng.normal(size=(n, k)), "p": rng.uniform(size=(m, k))}
+    if change:
+        change(vals)
+    F.prepare_row(MLOGREG, (m, n), [("rhs", (n, k)), ("kvec", (m, k))], "col_t", nnz=len(ci), rowptr64=rp64)
+    name = F.last_kernel()
+    assert name.startswith("fuse_row_mfma_pipe_")
+    kern = Kernels(F.last_source(), folder, [name])
+    a = Args()
+    side = [kern.copy(vals["v"]), kern.copy(vals["p"])]
+    rowptr, part = kern.copy(rp, np.int64 if rp64 else np.int32), kern.buffer((blocks, n, k))
+    x, colidx = kern.buffer(before + len(ci)), kern.buffer(before + len(ci), np.int32)
+    x[before:], colidx[before:] = vals["x"], ci
+    a.x, a.colidx, a.rowptr, a.partials = _ptr(x), _ptr(colidx), _ptr(rowptr), _ptr(part)
+    a.m, a.n, a.ld, a.nnz = m, n, n, before + len(ci)
+    for q, s in enumerate(side):
+        a.side[q], a.side_ld[q] = _ptr(s), k
+    kern.run(name, a, blocks, (kern.define("FUSE_NWAVE") + 1) * 64, last_first)
+    return part.sum(0), ops.make_csr(rp - before, ci, vals["x"], (m, n)), vals["v"], vals["p"]
+
+
+def test_csr_cells_at_the_end_of_32_bit_offsets(F, tmp_path, monkeypatch):
+    """The last cells of a matrix with 2^31 - 1 stored ones and 32-bit row offsets (address space only)."""
+    mask = np.random.default_rng(8).uniform(size=(41, 130)) < 0.2
+    got, x, v, p = _run_csr_pipe(F, tmp_path, monkeypatch, mask, 5, before=2 ** 31 - 1 - int(mask.sum()))
+    want = unfused.row_csr(MLOGREG, x, [("rhs", v), ("kvec", p)], "col_t").reshape(got.shape)
+    assert np.abs(got - want).max() <= 1e-12 * np.abs(want).max()
