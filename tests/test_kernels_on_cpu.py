@@ -80,6 +80,20 @@ def test_row_runs_read_side_inputs_of_existing_cells_only(F, tmp_path, monkeypat
     assert np.abs(got - want.reshape(got.shape)).max() <= 1e-12 * np.abs(want).max()
 
 
+@pytest.mark.parametrize("transposed", [False, True])
+@pytest.mark.parametrize("rp64", [False, True])
+def test_row_runs_in_either_order_of_the_lanes(F, tmp_path, monkeypatch, rp64, transposed):
+    """Lanes that run from the last one on between two meeting points: what one lane reads from LDS that another one of its wave
+    has written needs a barrier of the wave in between (the first panels' books)."""
+    rng = np.random.default_rng(4)
+    mask = rng.uniform(size=(23, 60)) < 0.4
+    if transposed:
+        mask = mask.T.copy()
+    body = [("uvdot",), ("main",), ("mul",), ("side", 0), ("add",)]
+    got, want = _run_row_runs(F, tmp_path, monkeypatch, body, "rowvec" if transposed else "colvec", transposed, 100, 11, 2, mask, rp64, 7, True)
+    assert np.abs(got - want.reshape(got.shape)).max() <= 1e-12 * np.abs(want).max()
+
+
 # --------------------------------------------------- matrix units over CSR rows, pipelined form --
 
 _Q = [("side", 1), ("main",), ("side", 0), ("matmult",), ("mul",)]
