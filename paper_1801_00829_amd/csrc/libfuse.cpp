@@ -1588,14 +1588,13 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
     // 1e5 x 1.5e4, rank 110 609 / 441; 2e4 x 4e4, rank 100 224 / 165 and 209 / 175; 2.7e4 x 1.2e5, rank 80 270 / 234 and 266 / 261;
     // but rank 64 at 1e5 x 1e5 562 / 561, rank 76 and 12 MB 151 / 160, 20 cells per row (2 per run) 275 / 284, 0.57 million cells
     // 50 / 71.
-    // (full_agg and no_agg, rank 100: 558 / 622 and 618 / 662 against the form above, which sums no products.)
     const int runs_mode = env_int("FUSE_OUTER_RUNS", 1);
     int runs_rb = 0;
-    if (runs_mode != 0 && panel_mode != 0 && kmode != 3 && (kmode == 2 || runs_mode == 2) && wrows > 0 && wcols > 0 && nvec <= 128 / VEC &&
+    if (runs_mode != 0 && panel_mode != 0 && kmode == 2 && wrows > 0 && wcols > 0 && nvec <= 128 / VEC &&
         (wcols - 1) * G_->ld + r < ((int64_t)1 << 28)) {          // (32-bit offsets into the gathered factor)
-        const int64_t row_bytes = nvec * VEC * 8 * (kmode == 2 ? 2 : 1);
+        const int64_t row_bytes = nvec * VEC * 8 * 2;
         const int64_t cell_bytes = X->rowptr_is64 ? 8 : 4;
-        // (beside the rows: the books of four panels, the block's sum)
+        // (beside the rows: the books of four panels)
         const int64_t cap = std::min<int64_t>(256, ((int64_t)160 * 1024 - 256) / (row_bytes + 4 * (4 + cell_bytes)));
         const int64_t blocks = std::max<int64_t>(8, rt.num_cus() / 8 * 8);
         const int64_t rounds = (wrows + blocks * cap - 1) / (blocks * cap);
@@ -1632,8 +1631,6 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
     // (waves x RC x rank doubles) must fit in 60 KB.
     int flat_rc = 0;
     panels = npanels > 0;
-    if (runs_rb)
-        stat_rcw = 0;
     if (panels && !stat_rcw && !runs_rb && env_int("FUSE_OUTER_FLAT", 1) != 0 &&
         (panel_mode == 2 || (double)X->nnz / (double)X->rows / (double)npanels <= 16.0)) {
         const double per_row_panel = (double)X->nnz / (double)X->rows / (double)npanels;

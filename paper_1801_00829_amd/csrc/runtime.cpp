@@ -194,7 +194,7 @@ int Runtime::load(Plan &p, Plan::Loaded &fn, std::string &err)
         (p.source.find("#define FUSE_PANELS 1") != std::string::npos || p.source.find("#define FUSE_PANELS 2") != std::string::npos ||
          p.source.find("#define FUSE_PANELS 3") != std::string::npos || p.source.find("#define FUSE_PANELS 4") != std::string::npos))
         e = hipModuleGetFunction(&l.prep, l.module, "fuse_outer_prep");
-    if (e == hipSuccess && p.source.find("#define FUSE_PANELS 4\n") != std::string::npos && p.source.find("#define FUSE_MODE 2\n") != std::string::npos)
+    if (e == hipSuccess && p.source.find("#define FUSE_PANELS 4\n") != std::string::npos)
         e = hipModuleGetFunction(&l.rows, l.module, "fuse_outer_rows");
     if (e != hipSuccess) {
         err = std::string("hipModuleGetFunction: ") + hipGetErrorString(e);

@@ -585,3 +585,14 @@ def test_code_objects_persist_in_the_cache_directory(F, tmp_path, monkeypatch):
     F.prepare_cell(body, (64, 64), [], "full")
     assert F.cache_disk_hits() == 0
     F.cache_clear()
+
+
+def test_row_runs_are_a_form_of_the_products_only(F, monkeypatch):
+    """Sums and values of Outer keep the panel walk that is faster for them, also where row runs are asked for."""
+    monkeypatch.setenv("FUSE_OUTER_RUNS", "2")
+    monkeypatch.setenv("FUSE_OUTER_PANELS", "2")
+    for agg, panels in (("full", "3"), ("none", "3"), ("right_mm", "4"), ("left_mm", "4")):
+        F.cache_clear()
+        F.prepare_outer([("main",), ("uvdot",), ("mul",)], (3000, 5000), 100, 300000, [], agg)
+        assert "#define FUSE_PANELS %s\n" % panels in F.last_source(), agg
+    assert "FUSE_MODE" not in F.last_source().split("#elif FUSE_PANELS == 4\n")[1].split("#endif   // FUSE_PANELS")[0]
