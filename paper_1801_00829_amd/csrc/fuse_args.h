@@ -28,8 +28,7 @@ typedef struct {
                                                  after the panel's first column ((npanels+1) x m offsets)         */
     int panel_w;                              /* Outer: columns per panel             */
     int pad_;
-    long long row_limit;                      /* Outer, row runs: cells of a row beyond which long_rows is set */
-    unsigned int *long_rows;                  /*   two words, the first 0 between calls                        */
+    long long row_limit;                      /* Outer, row runs: rows with more cells go to fuse_outer_rows */
     const int *side_ci[FUSE_MAX_SIDES];       /* sparse side inputs: column indices (values in side[], stored  */
     const void *side_rp[FUSE_MAX_SIDES];      /*   cells in side_ld[]), row offsets (int32 or int64)           */
 } fuse_kargs;

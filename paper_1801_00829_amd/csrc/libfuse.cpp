@@ -1587,7 +1587,7 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
     // 50 cells and 3e4 columns 547 / 373 and 579 / 391; 6e4 x 6e4, rank 90, 100 cells 640 / 441; 1.2e5 x 5e4, rank 110 1013 / 665;
     // 1e5 x 1.5e4, rank 110 609 / 441; 2e4 x 4e4, rank 100 224 / 165 and 209 / 175; 2.7e4 x 1.2e5, rank 80 270 / 234 and 266 / 261;
     // but rank 64 at 1e5 x 1e5 562 / 561, rank 76 and 12 MB 151 / 160, 20 cells per row (2 per run) 275 / 284, 0.57 million cells
-    // 50 / 71.
+    // 50 / 71.  (Even rows; rows far longer than the others go to a kernel of their own, see A.row_limit.)
     const int runs_mode = env_int("FUSE_OUTER_RUNS", 1);
     int runs_rb = 0;
     if (runs_mode != 0 && panel_mode != 0 && kmode == 2 && wrows > 0 && wcols > 0 && nvec <= 128 / VEC &&
@@ -1651,6 +1651,7 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
     const bool out_vec = vec2 && (!launch || aligned16(out));
     const int flat_wpe = std::max(1, std::min(8, env_int("FUSE_OUTER_WPE", 2)));      // waves per SIMD the flat form is built for (3: spills, 898 against 810 us)
     const int KBLOCK = stat_rcw || runs_rb ? SBLOCK : BLOCK;                // threads per block of the main kernel
+    const int RBLOCK = 512;                                                 // ... and of the one for long rows beside the row runs
     int sunr = env_int("FUSE_OUTER_SUNR", SBLOCK > 512 ? 1 : 2);  // steps of a wave whose gathers leave together (stationary form)
     sunr = (sunr >= 2 && G % 2 == 0) ? 2 : 1;
     const int uq = std::max(1, std::min(16, env_int("FUSE_OUTER_UQ", 4)));      // vectors of U per thread in flight while the rows are staged
@@ -1672,7 +1673,7 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
              "\n#define FUSE_NEED_COL " + std::to_string(need_col) + "\n#define FUSE_PANELS " + std::to_string(panels ? (runs_rb ? 4 : stat_rcw ? 3 : flat_rc ? 2 : 1) : 0) +
              "\n#define FUSE_RANK " + std::to_string(r) + "\n#define FUSE_RC " + std::to_string(std::max(flat_rc, 1)) +
              "\n#define FUSE_RB " + std::to_string(std::max(std::max(runs_rb, stat_rcw), 1)) + "\n#define FUSE_SUNR " + std::to_string(sunr) +
-             "\n#define FUSE_WPE " + std::to_string(stat_rcw || runs_rb ? SBLOCK / 256 : flat_wpe) + "\n#define FUSE_UQ " + std::to_string(uq) + "\n";
+             "\n#define FUSE_ROWS_BLOCK " + std::to_string(RBLOCK) + "\n#define FUSE_WPE " + std::to_string(stat_rcw || runs_rb ? SBLOCK / 256 : flat_wpe) + "\n#define FUSE_UQ " + std::to_string(uq) + "\n";
         s += side_tables(sides, nsides, prog.side_used);
         s += emit_outer_body(prog);
         s += kSrcOuter;
@@ -1773,7 +1774,7 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
         A.panel_ptr = ws.partials + part_doubles;
         if (fn.rows) {
             // a run of more than a wave's even share of its block's cells holds the block up: rows of a quarter more than that
-            A.long_rows = ws.ticket + 16;
+            // go to fuse_outer_rows (0.2 % of the rows at log-normal lengths)
             A.row_limit = runs_mode == 2 ? X->nnz : (int64_t)(1.25 * (double)X->nnz / (double)wrows * (double)std::max(runs_rb, KBLOCK / 64) / (double)(KBLOCK / 64)) + 16;
         }
         const int64_t gp = (wrows * 16 + 255) / 256;                 // 16 lanes per row
@@ -1782,8 +1783,8 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
     }
     if ((rc = rt.launch(fn.main, (unsigned)gx, 1, KBLOCK, stream, &A, sizeof A, g_err)) || !fn.rows)
         return rc;
-    const int64_t gr = std::max<int64_t>(1, std::min<int64_t>((wrows + 3) / 4, (int64_t)cus * env_int("FUSE_OUTER_BLOCKS_PER_CU", 8)));
-    return rt.launch(fn.rows, (unsigned)gr, 1, 256, stream, &A, sizeof A, g_err);
+    const int64_t gr = std::max<int64_t>(1, std::min<int64_t>(wrows, (int64_t)cus * 2));
+    return rt.launch(fn.rows, (unsigned)gr, 1, RBLOCK, stream, &A, sizeof A, g_err);
 }
 
 // values_only: the pattern exists, only the values of X are brought into its order again

@@ -22,7 +22,7 @@ class Args(ctypes.Structure):
                 ("out", ctypes.c_void_p), ("partials", ctypes.c_void_p), ("ticket", ctypes.c_void_p),
                 ("rank", ctypes.c_int), ("npanels", ctypes.c_int), ("panel_ptr", ctypes.c_void_p),
                 ("panel_w", ctypes.c_int), ("pad_", ctypes.c_int), ("row_limit", ctypes.c_longlong),
-                ("long_rows", ctypes.c_void_p), ("side_ci", ctypes.c_void_p * MAX_SIDES),
+                ("side_ci", ctypes.c_void_p * MAX_SIDES),
                 ("side_rp", ctypes.c_void_p * MAX_SIDES)]
 
 

@@ -758,6 +758,55 @@ def test_outer_row_runs_side_inputs_by_column(kind, agg, monkeypatch):
         assert_close(got, unfused.outer(body, ops.make_csr(rp, ci, va, (m, n)), u, v, sides, agg), tol=1e-12, what="row runs, %s" % kind)
 
 
+def _row_run_calls(F, body, x, xd, u, v):
+    """RIGHT_MM, LEFT_MM and LEFT_MM over a prepared pattern against the oracle."""
+    pattern = F.outer_left_prepare(xd)
+    for what, agg, got in (("right_mm", "right_mm", F.fuse_outer(body, xd, to_dev(u), to_dev(v), [], "right_mm")),
+                           ("left_mm", "left_mm", F.fuse_outer(body, xd, to_dev(u), to_dev(v), [], "left_mm")),
+                           ("left_mm, prepared", "left_mm", F.fuse_outer_left(body, xd, pattern, to_dev(u), to_dev(v)))):
+        assert_close(host(got), unfused.outer(body, x, u, v, [], agg), tol=1e-12, what="row runs, %s" % what)
+
+
+@pytest.mark.parametrize("rowptr64", [False, True])
+@pytest.mark.parametrize("r", [90, 101])
+def test_outer_row_runs_with_long_rows(r, rowptr64, monkeypatch):
+    """A few rows and columns far beyond what a wave takes (limit by the default rule: 1.25 x the mean x rows per block over
+    the waves, and 16), which another kernel sums, then a matrix without any on the same stream.  Tolerance as above."""
+    import paper_1801_00829_amd as F
+    monkeypatch.setenv("FUSE_OUTER_PANELS", "2")
+    body = [("main",), ("uvdot",), ("mul",), ("const", 0.5), ("add",)]
+    rng = np.random.default_rng(5400 + r)
+    for long_ones in (True, False, True):
+        m, n = 3000, 2500
+        mask = rng.uniform(size=(m, n)) < 0.002
+        if long_ones:
+            mask[[0, 1500, 1501, m - 1]] = True
+            mask[:, [0, 77, n - 1]] = True
+        rp, ci = np.concatenate([[0], np.cumsum(mask.sum(1))]), np.nonzero(mask)[1].astype(np.int32)
+        va = rng.uniform(0.1, 1.0, len(ci))
+        limit = 1.25 * len(ci) / min(m, n) * max(3000 / 256, 12) / 12 + 16          # at most, 256 blocks
+        assert (min(mask.sum(1).max(), mask.sum(0).max()) > limit) == long_ones
+        x = ops.make_csr(rp, ci, va, (m, n))
+        _row_run_calls(F, body, x, dev_csr(rp, ci, va, (m, n), rowptr64), rng.uniform(size=(m, r)), rng.uniform(size=(n, r)))
+
+
+@pytest.mark.parametrize("rowptr64", [False, True])
+def test_outer_row_runs_over_a_prepared_pattern(rowptr64, monkeypatch):
+    """Every call of the products takes the row runs, the one over a prepared pattern included.  Tolerance as above."""
+    import paper_1801_00829_amd as F
+    monkeypatch.setenv("FUSE_OUTER_PANELS", "2")
+    monkeypatch.setenv("FUSE_OUTER_RUNS", "2")
+    body = [("uvdot",), ("main",), ("mul",), ("const", 0.25), ("sub",)]
+    m, n, r = 700, 1300, 100
+    F.prepare_outer(body, (m, n), r, 60000, [], "left_mm", rowptr64)
+    assert "#define FUSE_PANELS 4\n" in F.last_source()         # (a body that no other test compiles)
+    rp, ci, va = W.csr_bernoulli(m, n, 0.07, 79)
+    rng = np.random.default_rng(5500)
+    _row_run_calls(F, body, ops.make_csr(rp, ci, va, (m, n)), dev_csr(rp, ci, va, (m, n), rowptr64), rng.uniform(size=(m, r)),
+                   rng.uniform(size=(n, r)))
+    assert "fuse_outer_rows" in F.last_source()
+
+
 def test_outer_right_mm_on_all_patterns():
     _outer_mm_on_all_patterns("right_mm", False, "")
 

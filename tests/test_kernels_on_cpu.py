@@ -23,7 +23,7 @@ def _ptr(a):
 
 # ------------------------------------------------------------------ outer products, row runs --
 
-def _run_row_runs(F, folder, monkeypatch, body, kind, transposed, r, rb, blocks, mask, rp64=False, width=3, last_first=False):
+def _run_row_runs(F, folder, monkeypatch, body, kind, transposed, r, rb, blocks, mask, rp64=False, width=3, last_first=False, row_limit=None):
     """RIGHT_MM over the cells that `mask` (m x n) has, with one side input of that kind: through the preparatory kernel, the main
     one with `blocks` blocks, and the one for long rows.  transposed: the kernels' LEFT_MM build, over the transposed matrix.  Returns
     (result, oracle)."""
@@ -61,11 +61,15 @@ def _run_row_runs(F, folder, monkeypatch, body, kind, transposed, r, rb, blocks,
     P = (wn + width - 1) // width
     pp = k.buffer((wm, P + 1), np.int64 if rp64 else np.int32)
     a.npanels, a.panel_w, a.panel_ptr = P, width, _ptr(pp)
-    a.long_rows = _ptr(keep["ticket"]) + 128
-    a.row_limit = len(wci)
+    a.row_limit = len(wci) if row_limit is None else row_limit
     k.run("fuse_outer_prep", a, (wm * 16 + 255) // 256, 256, last_first)
     k.run(name, a, blocks, k.define("FUSE_BLOCK"), last_first)
-    k.run("fuse_outer_rows", a, 2, 256, last_first)
+    if row_limit is not None:                       # the rows within the limit are complete, and nothing is handed on
+        short = np.diff(wrp) <= row_limit
+        want = unfused.outer(body, x, u, v, [(kind, side)], agg).reshape(wm, r)
+        err = np.abs(keep["out"] - want)[short].max(initial=0.0)
+        assert err <= 1e-12 * np.abs(want).max() and not keep["ticket"].any()
+    k.run("fuse_outer_rows", a, 3, k.define("FUSE_ROWS_BLOCK"), last_first)
     return keep["out"].copy(), unfused.outer(body, x, u, v, [(kind, side)], agg)
 
 
@@ -77,7 +81,8 @@ def test_row_runs_read_side_inputs_of_existing_cells_only(F, tmp_path, monkeypat
         mask[:, 0] = False, True                    # the walked matrix' first cell lies in the last row of the side
     body = [("uvdot",), ("main",), ("mul",), ("side", 0), ("add",)]
     got, want = _run_row_runs(F, tmp_path, monkeypatch, body, kind, transposed, 33, 4, 5, mask, width=1 if transposed else 3)
-    assert np.abs(got - want.reshape(got.shape)).max() <= 1e-12 * np.abs(want).max()
+    err = np.abs(got - want.reshape(got.shape)).max()
+    assert err <= 1e-12 * np.abs(want).max()
 
 
 @pytest.mark.parametrize("transposed", [False, True])
@@ -91,7 +96,25 @@ def test_row_runs_in_either_order_of_the_lanes(F, tmp_path, monkeypatch, rp64, t
         mask = mask.T.copy()
     body = [("uvdot",), ("main",), ("mul",), ("side", 0), ("add",)]
     got, want = _run_row_runs(F, tmp_path, monkeypatch, body, "rowvec" if transposed else "colvec", transposed, 100, 11, 2, mask, rp64, 7, True)
-    assert np.abs(got - want.reshape(got.shape)).max() <= 1e-12 * np.abs(want).max()
+    err = np.abs(got - want.reshape(got.shape)).max()
+    assert err <= 1e-12 * np.abs(want).max()
+
+
+@pytest.mark.parametrize("transposed", [False, True])
+@pytest.mark.parametrize("r", [33, 100])
+def test_row_runs_give_away_the_long_rows_only(F, tmp_path, monkeypatch, r, transposed):
+    """Rows beyond the limit -- the first, neighbours, the last, one without a rest for the waves -- are summed by the kernel
+    behind the row runs, all others by the row runs."""
+    rng = np.random.default_rng(6)
+    mask = rng.uniform(size=(31, 70)) < 0.1
+    mask[[0, 11, 12, 30]] = rng.uniform(size=(4, 70)) < 0.8
+    mask[20] = True
+    mask[5] = False
+    body = [("uvdot",), ("main",), ("mul",), ("side", 0), ("add",)]
+    got, want = _run_row_runs(F, tmp_path, monkeypatch, body, "matrix", transposed, r, 8, 2, mask.T.copy() if transposed else mask, width=9,
+                              row_limit=30)
+    err = np.abs(got - want.reshape(got.shape)).max()
+    assert err <= 1e-12 * np.abs(want).max()
 
 
 # --------------------------------------------------- matrix units over CSR rows, pipelined form --
@@ -134,4 +157,5 @@ def test_csr_cells_at_the_end_of_32_bit_offsets(F, tmp_path, monkeypatch):
     mask = np.random.default_rng(8).uniform(size=(41, 130)) < 0.2
     got, x, v, p = _run_csr_pipe(F, tmp_path, monkeypatch, mask, 5, before=2 ** 31 - 1 - int(mask.sum()))
     want = unfused.row_csr(MLOGREG, x, [("rhs", v), ("kvec", p)], "col_t").reshape(got.shape)
-    assert np.abs(got - want).max() <= 1e-12 * np.abs(want).max()
+    err = np.abs(got - want).max()
+    assert err <= 1e-12 * np.abs(want).max()
