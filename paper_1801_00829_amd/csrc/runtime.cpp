@@ -238,6 +238,14 @@ int Runtime::workspace(hipStream_t stream, size_t doubles, Workspace &ws, std::s
         err = std::string("hipGetDevice: ") + hipGetErrorString(e);
         return FUSE_ERUNTIME;
     }
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        Workspace &w = ws_[std::make_pair(dev, stream)];
+        if (!w.mu)
+            w.mu = std::make_shared<std::mutex>();
+        ws.mu = w.mu;
+    }
+    ws.in_use = std::unique_lock<std::mutex>(*ws.mu);       // (without mu_: its holder takes that as well)
     std::lock_guard<std::mutex> lk(mu_);
     Workspace &w = ws_[std::make_pair(dev, stream)];
     if (!w.ticket) {
@@ -267,7 +275,9 @@ int Runtime::workspace(hipStream_t stream, size_t doubles, Workspace &ws, std::s
         w.partials = np;
         w.partial_doubles = want;
     }
-    ws = w;
+    ws.partials = w.partials;
+    ws.partial_doubles = w.partial_doubles;
+    ws.ticket = w.ticket;
     return 0;
 }
 

@@ -31,10 +31,14 @@ struct Plan {
     std::map<int, Loaded> per_device;
 };
 
+// One stream's scratch memory.  A call that enqueues several kernels over it holds it until the last one is enqueued
+// (in_use), so calls that host threads make on one stream do not enqueue between each other's kernels.
 struct Workspace {
     double *partials = nullptr;
     size_t partial_doubles = 0;
     unsigned int *ticket = nullptr;
+    std::shared_ptr<std::mutex> mu;
+    std::unique_lock<std::mutex> in_use;
 };
 
 class Runtime {
@@ -78,7 +82,8 @@ public:
     int load(Plan &p, Plan::Loaded &fn, std::string &err);
     // The functions of a plan if it is already loaded on the current device (nothing is loaded here).
     bool loaded(Plan &p, Plan::Loaded &fn);
-    // Workspace of (current device, stream) with room for `doubles` partials.
+    // Workspace of (current device, stream) with room for `doubles` partials; waits for another thread's call that holds
+    // it.  Not twice in one call.
     int workspace(hipStream_t stream, size_t doubles, Workspace &ws, std::string &err);
     // Workgroups of `block` threads of kernel `f` that one compute unit holds at once (>= 1).
     int resident_blocks_per_cu(hipFunction_t f, int block);

@@ -807,6 +807,39 @@ def test_outer_row_runs_over_a_prepared_pattern(rowptr64, monkeypatch):
     assert "fuse_outer_rows" in F.last_source()
 
 
+def test_outer_products_from_two_threads_on_one_stream(monkeypatch):
+    """Two host threads, one stream, products that hand a panel table on between their kernels: every result is the one the
+    thread gets alone, bit for bit."""
+    import threading
+    import torch
+    import paper_1801_00829_amd as F
+    monkeypatch.setenv("FUSE_OUTER_PANELS", "2")
+    stream = torch.cuda.current_stream().cuda_stream
+    wrong = []
+
+    def calls(m, n, r, alone, go):
+        rp, ci, va = W.csr_bernoulli(m, n, 0.05, m)
+        x, u, v = dev_csr(rp, ci, va, (m, n), False), to_dev(rng_of[m].uniform(size=(m, r))), to_dev(rng_of[m].uniform(size=(n, r)))
+        want = F.fuse_outer(ALS_W, x, u, v, [], "right_mm", stream=stream).clone()
+        torch.cuda.synchronize()
+        alone.wait()
+        go.wait()
+        got = [F.fuse_outer(ALS_W, x, u, v, [], "right_mm", stream=stream) for _ in range(200)]
+        torch.cuda.synchronize()
+        wrong.extend(i for i, g in enumerate(got) if not torch.equal(g, want))
+
+    rng_of = {600: np.random.default_rng(1), 1500: np.random.default_rng(2)}
+    alone, go = threading.Barrier(3), threading.Barrier(3)
+    threads = [threading.Thread(target=calls, args=(m, n, 100, alone, go)) for m, n in ((600, 3000), (1500, 800))]
+    for t in threads:
+        t.start()
+    alone.wait()
+    go.wait()
+    for t in threads:
+        t.join()
+    assert not wrong, len(wrong)
+
+
 def test_outer_right_mm_on_all_patterns():
     _outer_mm_on_all_patterns("right_mm", False, "")
 

@@ -4,6 +4,7 @@ for gfx950 (hipRTC needs no device), plan-cache behaviour."""
 import ctypes
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -596,3 +597,13 @@ def test_row_runs_are_a_form_of_the_products_only(F, monkeypatch):
         F.prepare_outer([("main",), ("uvdot",), ("mul",)], (3000, 5000), 100, 300000, [], agg)
         assert "#define FUSE_PANELS %s\n" % panels in F.last_source(), agg
     assert "FUSE_MODE" not in F.last_source().split("#elif FUSE_PANELS == 4\n")[1].split("#endif   // FUSE_PANELS")[0]
+
+
+def test_calls_on_one_stream_hold_its_workspace(F, tmp_path):
+    """Kernels of one call hand results on through the stream's workspace: another thread's call on the stream has to wait
+    until all of them are enqueued (workspace_hold.cpp)."""
+    exe = str(tmp_path / "workspace_hold")
+    subprocess.run(["/opt/rocm/bin/hipcc", "-std=c++17", "-O1", "--offload-arch=gfx950", "-rdynamic", os.path.join(ROOT, "tests", "workspace_hold.cpp"),
+                    "-L" + os.path.dirname(F.lib_path()), "-l:libfuse.so", "-lpthread", "-o", exe, "-Wl,-rpath," + os.path.dirname(F.lib_path())], check=True)
+    r = subprocess.run([exe], timeout=60, capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
