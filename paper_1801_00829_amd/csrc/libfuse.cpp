@@ -1410,6 +1410,20 @@ LeftPattern left_pattern_layout(const fuse_csr *X)
     return l;
 }
 
+// Whether a product gains from walking its matrix in column panels (row runs): enough cells to fill them, and a gathered factor,
+// `rows` rows of row_bytes each (what is read of them, whatever their pitch), beyond the L2s.
+bool outer_panels_pay(int64_t nnz, int64_t rows, int64_t row_bytes)
+{
+    return nnz >= 1500000 && rows * row_bytes > (int64_t)env_int("FUSE_OUTER_PANEL_MIN_KB", 12288) * 1024;
+}
+
+// Whether a prepared pattern is ordered so that its panels can be walked: before U and V are known, for the widest rows that
+// a wave takes.
+bool outer_pattern_grouped(const fuse_csr *X)
+{
+    return env_int("FUSE_OUTER_PANELS", 1) == 2 || outer_panels_pay(X->nnz, X->rows, 128 * 8);
+}
+
 // pattern: a prepared left_mm pattern of X (device), or nullptr
 int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, const fuse_dense *V,
                const fuse_side *sides, int nsides, int agg, double *out, void *stream_, bool launch,
@@ -1592,33 +1606,33 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
     int runs_rb = 0;
     if (runs_mode != 0 && panel_mode != 0 && kmode == 2 && wrows > 0 && wcols > 0 && nvec <= 128 / VEC &&
         (wcols - 1) * G_->ld + r < ((int64_t)1 << 28)) {          // (32-bit offsets into the gathered factor)
-        const int64_t row_bytes = nvec * VEC * 8 * 2;
+        const int64_t row_bytes = nvec * VEC * 8;
         const int64_t cell_bytes = X->rowptr_is64 ? 8 : 4;
         // (beside the rows: the books of four panels)
-        const int64_t cap = std::min<int64_t>(256, ((int64_t)160 * 1024 - 256) / (row_bytes + 4 * (4 + cell_bytes)));
+        const int64_t cap = std::min<int64_t>(256, ((int64_t)160 * 1024 - 256) / (2 * row_bytes + 4 * (4 + cell_bytes)));
         const int64_t blocks = std::max<int64_t>(8, rt.num_cus() / 8 * 8);
         const int64_t rounds = (wrows + blocks * cap - 1) / (blocks * cap);
         int64_t rb = (wrows + rounds * blocks - 1) / (rounds * blocks);
         if (env_int("FUSE_OUTER_RB", 0) > 0)
             rb = std::min<int64_t>(cap, env_int("FUSE_OUTER_RB", 0));
-        const int64_t vbytes = wcols * G_->ld * 8;
         const double per_row = (double)X->nnz / (double)wrows;
         // Columns per panel: a wave's share of a panel comes in units of up to 64 cells, about 50 of them leave room for the
         // shares' spread; as many units as make 4.5 MB of V, at most 8 MB.  1e5 x 1e5, rank 100, 4 / 5 / 6.5 / 8 / 10 MB: 781 / 727 / 744 /
         // 806 / 864 us; 2.7e4 x 1.2e5, rank 80: 225 / 227 / 212 / 206 / 217; 20 cells per row: 348 / 309 / 269 / 267 / 253.
         double w = (double)wcols * 50.0 * (SBLOCK / 64) / std::max(1.0, per_row * (double)rb);
-        w *= std::max(1.0, std::ceil(4.5e6 / (w * (double)(G_->ld * 8))));
+        w *= std::max(1.0, std::ceil(4.5e6 / (w * (double)row_bytes)));
         const int64_t pkb = env_int("FUSE_OUTER_RPANEL_KB", 0);
-        w = pkb > 0 ? (double)(pkb * 1024) / (double)(G_->ld * 8) : std::min(w, 8.0e6 / (double)(G_->ld * 8));
-        const int64_t grain = !transposed ? 1 : transpose_row_grain(X->rows, X->cols, X->nnz);
-        if (grain > 0 && (vbytes > (int64_t)env_int("FUSE_OUTER_PANEL_MIN_KB", 12288) * 1024 || panel_mode == 2)) {
+        w = pkb > 0 ? (double)(pkb * 1024) / (double)row_bytes : std::min(w, 8.0e6 / (double)row_bytes);
+        const int64_t grain = !transposed ? 1 : with_pattern && !outer_pattern_grouped(X) ? 0 : transpose_row_grain(X->rows, X->cols, X->nnz);
+        const bool pays = outer_panels_pay(X->nnz, wcols, row_bytes);
+        if (grain > 0 && (runs_mode == 2 || panel_mode == 2 || pays)) {
             int64_t W = std::max<int64_t>(1, std::min<int64_t>((int64_t)w, panel_mode == 2 ? (wcols + 7) / 8 : wcols));
             W = std::max<int64_t>(grain, (W + grain / 2) / grain * grain);
             W = std::max<int64_t>(W, (wcols + 1023) / 1024);
             W = (W + grain - 1) / grain * grain;
             const int64_t P = (wcols + W - 1) / W;
             if (P >= 2 && (P + 1) * wrows * cell_bytes <= ((int64_t)1 << 30) &&
-                (runs_mode == 2 || panel_mode == 2 || (per_row / (double)P >= 3.0 && r >= 80 && X->nnz >= 1500000))) {
+                (runs_mode == 2 || panel_mode == 2 || (per_row / (double)P >= 3.0 && r >= 80))) {
                 runs_rb = (int)rb;
                 npanels = (int)P;
                 panel_w = (int)W;
@@ -1754,7 +1768,7 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
         int *trow = reinterpret_cast<int *>(base + t_scratch + t_ptr);
         double *tval = base + t_scratch + t_ptr + t_row;
         if (transpose_launch(X->rowptr, X->rowptr_is64, X->colidx, X->vals, X->rows, X->cols, X->nnz, scratch, tptr,
-                             trow, tval, stream))
+                             trow, tval, runs_rb > 0, stream))
             return fail(FUSE_ERUNTIME, "left_mm: launching the pattern transposition failed");
         A.x = tval;
         A.colidx = trow;
@@ -1818,7 +1832,8 @@ int outer_left_prepare_impl(const fuse_csr *X, void *pattern, void *stream_, boo
     double *iota = ws.partials + 64 + scratch;
     if (iota_launch(iota, X->nnz, stream) ||
         transpose_launch(X->rowptr, X->rowptr_is64, X->colidx, iota, X->rows, X->cols, X->nnz, ws.partials + 64, base,
-                         reinterpret_cast<int *>(base + lp.ptr), base + lp.ptr + lp.row, stream))
+                         reinterpret_cast<int *>(base + lp.ptr), base + lp.ptr + lp.row,
+                         outer_pattern_grouped(X), stream))
         return fail(FUSE_ERUNTIME, "fuse_outer_left_prepare: launching the pattern transposition failed");
     if (gather_launch(base + lp.ptr + lp.row + lp.perm, X->vals, base + lp.ptr + lp.row, X->nnz, stream))
         return fail(FUSE_ERUNTIME, "fuse_outer_left_prepare: launch failed");

@@ -128,10 +128,10 @@ int check_csr_launch(const void *rowptr, int rowptr_is64, const int *colidx, lon
 // transpose_scratch_bytes() bytes, 16-byte aligned.  0 on success.
 size_t transpose_scratch_bytes(long long m, long long n, long long nnz, int rowptr_is64);
 int transpose_launch(const void *rowptr, int rowptr_is64, const int *colidx, const double *vals, long long m, long long n,
-                     long long nnz, void *scratch, void *tptr, int *trow, double *tval, hipStream_t stream);
+                     long long nnz, void *scratch, void *tptr, int *trow, double *tval, bool grouped, hipStream_t stream);
 
-// Within a column of the transposed matrix the cells are ordered by groups of this many rows of the original one
-// (and not inside a group); 0: not at all.
+// With `grouped` the cells within a column of the transposed matrix are ordered by groups of this many rows of the original
+// one (and not inside a group); 0: never.
 long long transpose_row_grain(long long m, long long n, long long nnz);
 
 int iota_launch(double *dst, long long n, hipStream_t stream);     // dst[i] = (double)i

@@ -10,8 +10,8 @@
 //      the first group are the column offsets of the transposed matrix -- and moves (row, value) to their final places.
 // Matrices with more than 1024 * 8192 columns take the plain form instead: one global atomic per
 // cell for the counts and one for the places.  The order of the cells of a column inside a group of rows (in the
-// plain form: inside the column) is whatever the atomics produce.  The groups -- as many as the counters have room for, at most
-// 128 -- let the column-panel kernels of Outer walk the result: a panel is a whole number of groups.
+// plain form: inside the column) is whatever the atomics produce.  The groups -- one, or as many as the counters have room for,
+// at most 128 -- let the column-panel kernels of Outer walk the result: a panel is a whole number of groups.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -304,7 +304,7 @@ struct Shape {                   // launch shape of the two-level form
     long long rows_per_block, nblk, nhist;
 };
 
-Shape shape_of(long long m, long long n, long long nnz)
+Shape shape_of(long long m, long long n, long long nnz, bool grouped)
 {
     Shape s = {};
     int shift = 0;
@@ -314,10 +314,8 @@ Shape shape_of(long long m, long long n, long long nnz)
     s.two_level = shift <= MAX_RANGE_SHIFT && nnz < 4294967296LL && !(plain && plain[0] == '1');
     s.shift = shift;
     s.nranges = (int)((n + (1LL << shift) - 1) >> shift);
-    // (groups only where a product would walk panels of the result: 1.5 million cells and 12 MB of rows of at most 128 columns;
-    // they cost a small matrix 70 us of preparation.  FUSE_OUTER_PANELS=2: panels on small inputs)
-    const char *panels = std::getenv("FUSE_OUTER_PANELS");
-    const bool grouped = (nnz >= 1500000 && m * 1024 > (12LL << 20)) || (panels && panels[0] == '2');
+    // (groups only where the caller walks panels of the result: 1e5 x 1e5, 1e7 cells 566 us without and 600 us with them, 2e4 x
+    // 4e4, 2e6 cells 88 and 96; a small matrix would pay 70 us)
     const int most = grouped ? std::max(1, std::min(MAX_GROUPS, RANGE_COUNTERS >> shift)) : 1;
     while (((m - 1) >> s.group_shift) >= most)
         ++s.group_shift;
@@ -334,10 +332,10 @@ size_t align16(size_t b) { return (b + 15) / 16 * 16; }
 
 template <typename RP, typename XRP>
 int transpose_typed(const void *rowptr, const int *colidx, const double *vals, long long m, long long n, long long nnz,
-                    char *scratch, void *tptr_, int *trow, double *tval, hipStream_t stream)
+                    char *scratch, void *tptr_, int *trow, double *tval, bool grouped, hipStream_t stream)
 {
     RP *tptr = (RP *)tptr_;
-    const Shape sh = shape_of(m, n, nnz);
+    const Shape sh = shape_of(m, n, nnz, grouped);
     if (!sh.two_level) {
         RP *next = (RP *)scratch, *bsum = (RP *)(scratch + align16((size_t)n * sizeof(RP)));
         const long long nb = (n + SCAN_CHUNK - 1) / SCAN_CHUNK;
@@ -418,14 +416,14 @@ long long transpose_row_grain(long long m, long long n, long long nnz)
 {
     if (m <= 0 || n <= 0)
         return 0;
-    const Shape sh = shape_of(m, n, nnz);
+    const Shape sh = shape_of(m, n, nnz, true);
     return sh.two_level ? 1LL << sh.group_shift : 0;
 }
 
 size_t transpose_scratch_bytes(long long m, long long n, long long nnz, int rowptr_is64)
 {
     const size_t rpb = rowptr_is64 ? 8 : 4;
-    const Shape sh = shape_of(m, n, nnz);
+    const Shape sh = shape_of(m, n, nnz, false);          // (the groups are counted in LDS)
     if (!sh.two_level)
         return align16((size_t)n * rpb) + align16((size_t)((n + SCAN_CHUNK - 1) / SCAN_CHUNK) * rpb);
     const long long nb = (sh.nhist + SCAN_CHUNK - 1) / SCAN_CHUNK;
@@ -433,14 +431,14 @@ size_t transpose_scratch_bytes(long long m, long long n, long long nnz, int rowp
 }
 
 int transpose_launch(const void *rowptr, int rowptr_is64, const int *colidx, const double *vals, long long m, long long n,
-                     long long nnz, void *scratch, void *tptr, int *trow, double *tval, hipStream_t stream)
+                     long long nnz, void *scratch, void *tptr, int *trow, double *tval, bool grouped, hipStream_t stream)
 {
     if (m <= 0 || n <= 0 || m > 2147483647LL / 16)
         return -1;
     if (rowptr_is64)
         return transpose_typed<unsigned long long, long long>(rowptr, colidx, vals, m, n, nnz, (char *)scratch, tptr, trow, tval,
-                                                              stream);
-    return transpose_typed<unsigned int, int>(rowptr, colidx, vals, m, n, nnz, (char *)scratch, tptr, trow, tval, stream);
+                                                              grouped, stream);
+    return transpose_typed<unsigned int, int>(rowptr, colidx, vals, m, n, nnz, (char *)scratch, tptr, trow, tval, grouped, stream);
 }
 
 }  // namespace fuse

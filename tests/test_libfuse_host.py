@@ -607,3 +607,19 @@ def test_calls_on_one_stream_hold_its_workspace(F, tmp_path):
                     "-L" + os.path.dirname(F.lib_path()), "-l:libfuse.so", "-lpthread", "-o", exe, "-Wl,-rpath," + os.path.dirname(F.lib_path())], check=True)
     r = subprocess.run([exe], timeout=60, capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+@pytest.mark.parametrize("rows,ld,panels", [(12000, 100, 0), (12000, 200, 0), (16500, 100, 4), (16500, 200, 4)])
+def test_row_runs_go_by_the_bytes_of_the_gathered_rows(F, rows, ld, panels):
+    """The same form for a factor and for a view of wider rows, and the same for RIGHT_MM and its mirrored LEFT_MM, whose
+    transposed pattern has to be ordered for it."""
+    import paper_1801_00829_amd._lib as L
+    from paper_1801_00829_amd import api
+    lib, r, other, nnz = L.load(), 100, 30000, 3000000
+    e, keep = api._expr([("main",), ("uvdot",), ("mul",)])
+    for agg, m, n in (("right_mm", other, rows), ("left_mm", rows, other)):
+        F.cache_clear()
+        x = L.CsrDesc(None, None, None, 0, m, n, nnz)
+        u, v = L.Dense(None, m, r, ld), L.Dense(None, n, r, ld)
+        assert lib.fuse_prepare_outer(ctypes.byref(e), ctypes.byref(x), ctypes.byref(u), ctypes.byref(v), None, 0, F.AGG[agg]) == 0
+        assert "#define FUSE_PANELS %d\n" % panels in F.last_source(), agg
