@@ -1605,7 +1605,7 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
     const int runs_mode = env_int("FUSE_OUTER_RUNS", 1);
     int runs_rb = 0;
     if (runs_mode != 0 && panel_mode != 0 && kmode == 2 && wrows > 0 && wcols > 0 && nvec <= 128 / VEC &&
-        (wcols - 1) * G_->ld + r < ((int64_t)1 << 28)) {          // (32-bit offsets into the gathered factor)
+        (wcols - 1) * G_->ld + r <= ((int64_t)1 << 28) - 2) {          // (31-bit offsets; lanes past a row's end load from byte 2^31 - 16 on)
         const int64_t row_bytes = nvec * VEC * 8;
         const int64_t cell_bytes = X->rowptr_is64 ? 8 : 4;
         // (beside the rows: the books of four panels)

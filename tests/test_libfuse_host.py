@@ -623,3 +623,19 @@ def test_row_runs_go_by_the_bytes_of_the_gathered_rows(F, rows, ld, panels):
         u, v = L.Dense(None, m, r, ld), L.Dense(None, n, r, ld)
         assert lib.fuse_prepare_outer(ctypes.byref(e), ctypes.byref(x), ctypes.byref(u), ctypes.byref(v), None, 0, F.AGG[agg]) == 0
         assert "#define FUSE_PANELS %d\n" % panels in F.last_source(), agg
+
+
+def test_row_runs_need_offsets_below_their_place_outside_the_factor(F, monkeypatch):
+    """Lanes past the end of a row load from byte 2^31 - 16 on, which has to lie behind a gathered factor of any size."""
+    import paper_1801_00829_amd._lib as L
+    from paper_1801_00829_amd import api
+    monkeypatch.setenv("FUSE_OUTER_PANELS", "2")
+    lib, m, n, r = L.load(), 3000, 3, 101
+    e, keep = api._expr([("main",), ("uvdot",), ("mul",)])
+    for last, panels in ((2 ** 28 - 3, 4), (2 ** 28 - 1, 0)):          # values up to the end of the last row
+        F.cache_clear()
+        x, u = L.CsrDesc(None, None, None, 0, m, n, 6000), L.Dense(None, m, r, r)
+        v = L.Dense(None, n, r, (last - r) // (n - 1))
+        assert (n - 1) * v.ld + r == last
+        assert lib.fuse_prepare_outer(ctypes.byref(e), ctypes.byref(x), ctypes.byref(u), ctypes.byref(v), None, 0, F.AGG["right_mm"]) == 0
+        assert "#define FUSE_PANELS %d\n" % panels in F.last_source(), last
