@@ -27,7 +27,7 @@ typedef struct {
     void *panel_ptr;                          /* Outer workspace: per panel and row, the first stored cell at or
                                                  after the panel's first column ((npanels+1) x m offsets)         */
     int panel_w;                              /* Outer: columns per panel             */
-    int pad_;
+    int block_rows;                           /* Outer, row runs: rows of a block per round (<= FUSE_RB) */
     long long row_limit;                      /* Outer, row runs: rows with more cells go to fuse_outer_rows */
     const int *side_ci[FUSE_MAX_SIDES];       /* sparse side inputs: column indices (values in side[], stored  */
     const void *side_rp[FUSE_MAX_SIDES];      /*   cells in side_ld[]), row offsets (int32 or int64)           */

@@ -1603,7 +1603,7 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
     // but rank 64 at 1e5 x 1e5 562 / 561, rank 76 and 12 MB 151 / 160, 20 cells per row (2 per run) 275 / 284, 0.57 million cells
     // 50 / 71.  (Even rows; rows far longer than the others go to a kernel of their own, see A.row_limit.)
     const int runs_mode = env_int("FUSE_OUTER_RUNS", 1);
-    int runs_rb = 0;
+    int runs_rb = 0, runs_cap = 1;       // rows per block and round, and of how many the plan has room for (two plans, whatever the rows)
     if (runs_mode != 0 && panel_mode != 0 && kmode == 2 && wrows > 0 && wcols > 0 && nvec <= 128 / VEC &&
         (wcols - 1) * G_->ld + r <= ((int64_t)1 << 28) - 2) {          // (31-bit offsets; lanes past a row's end load from byte 2^31 - 16 on)
         const int64_t row_bytes = nvec * VEC * 8;
@@ -1634,6 +1634,7 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
             if (P >= 2 && (P + 1) * wrows * cell_bytes <= ((int64_t)1 << 30) &&
                 (runs_mode == 2 || panel_mode == 2 || (per_row / (double)P >= 3.0 && r >= 80))) {
                 runs_rb = (int)rb;
+                runs_cap = (int)(rb <= 64 ? std::min<int64_t>(64, cap) : cap);
                 npanels = (int)P;
                 panel_w = (int)W;
             }
@@ -1669,7 +1670,7 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
     int sunr = env_int("FUSE_OUTER_SUNR", SBLOCK > 512 ? 1 : 2);  // steps of a wave whose gathers leave together (stationary form)
     sunr = (sunr >= 2 && G % 2 == 0) ? 2 : 1;
     const int uq = std::max(1, std::min(16, env_int("FUSE_OUTER_UQ", 4)));      // vectors of U per thread in flight while the rows are staged
-    const std::string key = std::string("outer|") + (panels ? (runs_rb ? "runs" + std::to_string(runs_rb) + "r" + std::to_string(r) + "|" : stat_rcw ? "stat" + std::to_string(stat_rcw) + "r" + std::to_string(r) + "u" + std::to_string(sunr) + "q" + std::to_string(uq) + "|"
+    const std::string key = std::string("outer|") + (panels ? (runs_rb ? "runs" + std::to_string(runs_cap) + "r" + std::to_string(r) + "|" : stat_rcw ? "stat" + std::to_string(stat_rcw) + "r" + std::to_string(r) + "u" + std::to_string(sunr) + "q" + std::to_string(uq) + "|"
                                                              : flat_rc ? "flat" + std::to_string(flat_rc) + "r" + std::to_string(r) + "w" + std::to_string(flat_wpe) + "|" : std::string("panels|")) : std::string("")) + prog.key + "|" + side_key(sides, nsides) + "|agg" +
                             std::to_string(kmode) + (transposed ? "T" : "") + (kmode == 2 && out_vec ? "o" : "") + "|v" + std::to_string(VEC) + "g" + std::to_string(G) + "e" +
                             std::to_string(EPL) + "u" + std::to_string(UNR) + "b" + std::to_string(KBLOCK) + "w" +
@@ -1686,7 +1687,7 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
              std::to_string(kmode) + "\n#define FUSE_TRANSPOSED " + std::to_string(transposed) + "\n#define FUSE_OUT_VEC " + std::to_string(out_vec) + "\n#define FUSE_RP64 " + std::to_string(X->rowptr_is64 != 0) +
              "\n#define FUSE_NEED_COL " + std::to_string(need_col) + "\n#define FUSE_PANELS " + std::to_string(panels ? (runs_rb ? 4 : stat_rcw ? 3 : flat_rc ? 2 : 1) : 0) +
              "\n#define FUSE_RANK " + std::to_string(r) + "\n#define FUSE_RC " + std::to_string(std::max(flat_rc, 1)) +
-             "\n#define FUSE_RB " + std::to_string(std::max(std::max(runs_rb, stat_rcw), 1)) + "\n#define FUSE_SUNR " + std::to_string(sunr) +
+             "\n#define FUSE_RB " + std::to_string(runs_rb ? runs_cap : std::max(stat_rcw, 1)) + "\n#define FUSE_SUNR " + std::to_string(sunr) +
              "\n#define FUSE_ROWS_BLOCK " + std::to_string(RBLOCK) + "\n#define FUSE_WPE " + std::to_string(stat_rcw || runs_rb ? SBLOCK / 256 : flat_wpe) + "\n#define FUSE_UQ " + std::to_string(uq) + "\n";
         s += side_tables(sides, nsides, prog.side_used);
         s += emit_outer_body(prog);
@@ -1786,6 +1787,7 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
         A.npanels = npanels;
         A.panel_w = panel_w;
         A.panel_ptr = ws.partials + part_doubles;
+        A.block_rows = runs_rb;
         if (fn.rows) {
             // a run of more than a wave's even share of its block's cells holds the block up: rows of a quarter more than that
             // go to fuse_outer_rows (0.2 % of the rows at log-normal lengths)

@@ -21,7 +21,7 @@ class Args(ctypes.Structure):
                 ("m", ctypes.c_longlong), ("n", ctypes.c_longlong), ("ld", ctypes.c_longlong), ("nnz", ctypes.c_longlong),
                 ("out", ctypes.c_void_p), ("partials", ctypes.c_void_p), ("ticket", ctypes.c_void_p),
                 ("rank", ctypes.c_int), ("npanels", ctypes.c_int), ("panel_ptr", ctypes.c_void_p),
-                ("panel_w", ctypes.c_int), ("pad_", ctypes.c_int), ("row_limit", ctypes.c_longlong),
+                ("panel_w", ctypes.c_int), ("block_rows", ctypes.c_int), ("row_limit", ctypes.c_longlong),
                 ("side_ci", ctypes.c_void_p * MAX_SIDES),
                 ("side_rp", ctypes.c_void_p * MAX_SIDES)]
 

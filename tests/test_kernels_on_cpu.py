@@ -38,6 +38,7 @@ def _run_row_runs(F, folder, monkeypatch, body, kind, transposed, r, rb, blocks,
     u, v = rng.uniform(size=(m, r)), rng.uniform(size=(n, r))
     side = rng.uniform(size={"matrix": (m, n), "colvec": (m, 1), "rowvec": (1, n)}[kind])
     agg = "left_mm" if transposed else "right_mm"
+    F.cache_clear()                                 # (the source of the last plan that was compiled is wanted)
     F.prepare_outer(body, (m, n), r, max(len(ci), 1), [(kind, None)], agg, rp64)
     name = F.last_kernel()
     k = Kernels(F.last_source(), folder, [name, "fuse_outer_prep", "fuse_outer_rows"])
@@ -60,7 +61,7 @@ def _run_row_runs(F, folder, monkeypatch, body, kind, transposed, r, rb, blocks,
     a.m, a.n, a.nnz = wm, wn, len(wci)
     P = (wn + width - 1) // width
     pp = k.buffer((wm, P + 1), np.int64 if rp64 else np.int32)
-    a.npanels, a.panel_w, a.panel_ptr = P, width, _ptr(pp)
+    a.npanels, a.panel_w, a.panel_ptr, a.block_rows = P, width, _ptr(pp), rb
     a.row_limit = len(wci) if row_limit is None else row_limit
     k.run("fuse_outer_prep", a, (wm * 16 + 255) // 256, 256, last_first)
     k.run(name, a, blocks, k.define("FUSE_BLOCK"), last_first)
@@ -135,6 +136,7 @@ def _run_csr_pipe(F, folder, monkeypatch, mask, k, rp64=False, before=0, blocks=
     vals = {"x": rng.uniform(0.1, 1.0, len(ci)), "v": rng.normal(size=(n, k)), "p": rng.uniform(size=(m, k))}
     if change:
         change(vals)
+    F.cache_clear()
     F.prepare_row(MLOGREG, (m, n), [("rhs", (n, k)), ("kvec", (m, k))], "col_t", nnz=len(ci), rowptr64=rp64)
     name = F.last_kernel()
     assert name.startswith("fuse_row_mfma_pipe_")

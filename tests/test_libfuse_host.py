@@ -639,3 +639,14 @@ def test_row_runs_need_offsets_below_their_place_outside_the_factor(F, monkeypat
         assert (n - 1) * v.ld + r == last
         assert lib.fuse_prepare_outer(ctypes.byref(e), ctypes.byref(x), ctypes.byref(u), ctypes.byref(v), None, 0, F.AGG["right_mm"]) == 0
         assert "#define FUSE_PANELS %d\n" % panels in F.last_source(), last
+
+
+def test_row_runs_plans_do_not_depend_on_the_number_of_rows(F):
+    """Matrices of one program differ in their rows: two plans (up to 64 rows per block and more), not one per row count."""
+    F.cache_clear()
+    for agg in ("right_mm", "left_mm"):
+        for rows in (20000, 21111, 30000, 45000, 60001, 77777, 100000, 120000):
+            shape = (rows, 40000) if agg == "right_mm" else (40000, rows)
+            F.prepare_outer([("main",), ("uvdot",), ("mul",)], shape, 100, 4000000, [], agg)
+            assert "#define FUSE_PANELS 4\n" in F.last_source()
+    assert F.cache_stats()[1] <= 4
