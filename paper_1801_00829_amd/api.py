@@ -289,9 +289,10 @@ _ROW_COUNT_KINDS = frozenset(("matrix", "colvec", "rowvec", "scalar"))
 
 
 def _row_count(lib, e, expr, xd, xs, sides, sa, ns, agg):
-    """_row_out_count, kept by value of what it depends on (sides without a shape of their own: their kinds)."""
+    """_row_out_count, kept by value of what it depends on (sides without a shape of their own: their kinds; tokens that can
+    be read again)."""
     kinds = tuple([s[0] for s in sides])
-    if not _ROW_COUNT_KINDS.issuperset(kinds):
+    if not _ROW_COUNT_KINDS.issuperset(kinds) or not isinstance(expr, (list, tuple)):
         return _row_out_count(lib, e, xd, xs, sa, ns, agg)
     try:
         key = (tuple(expr), kinds, agg, xd.rows, xd.cols, -1) if xs is None else (tuple(expr), kinds, agg, xs.rows, xs.cols, xs.nnz)

@@ -650,3 +650,19 @@ def test_row_runs_plans_do_not_depend_on_the_number_of_rows(F):
             F.prepare_outer([("main",), ("uvdot",), ("mul",)], shape, 100, 4000000, [], agg)
             assert "#define FUSE_PANELS 4\n" in F.last_source()
     assert F.cache_stats()[1] <= 4
+
+
+def test_row_counts_are_kept_for_expressions_that_can_be_read_again(F):
+    """An iterator over tokens is used up once its descriptor is found; its result count must not be taken from, or kept for,
+    the tokens that are left in it (none)."""
+    import paper_1801_00829_amd._lib as L
+    from paper_1801_00829_amd import api
+    per_row, per_cell = [("main",), ("rowsum",)], [("main",), ("pow2",)]
+    xd = L.Dense(None, 30, 7, 7)
+    sa, ns = api._sides([], 30, 7)
+    for expr, count in ((per_row, 30), (per_cell, 210)) * 2:
+        e, keep = api._expr(expr)
+        it = iter(expr)
+        assert api._expr(it)[0] is e
+        assert api._row_count(L.load(), e, it, xd, None, [], sa, ns, "none") == count
+        assert api._row_count(L.load(), e, expr, xd, None, [], sa, ns, "none") == count
