@@ -168,12 +168,15 @@ def _csr(x):
                      1 if rowptr.dtype == torch.int64 else 0, m, n, vals.numel())
 
 
+# the handle of a device's current stream without an object for it (not part of torch's public interface)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream):
     if stream is None:
-        # the current stream of the current device, without an object for it.  (Small operators are bound by this module: cell over
-        # 100 x 100 14.2 us per call with a stream object, a descriptor key built token by token and each tensor's shape and
-        # strides asked for several times, 9.5 us now; row 17.6 and 14.7 with the library's result count kept by value.)
-        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+        if _raw_stream is not None:
+            return ctypes.c_void_p(_raw_stream(torch.cuda.current_device()))
+        stream = torch.cuda.current_stream()
     return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
 
 

@@ -666,3 +666,17 @@ def test_row_counts_are_kept_for_expressions_that_can_be_read_again(F):
         assert api._expr(it)[0] is e
         assert api._row_count(L.load(), e, it, xd, None, [], sa, ns, "none") == count
         assert api._row_count(L.load(), e, expr, xd, None, [], sa, ns, "none") == count
+
+
+def test_binding_finds_the_current_stream_without_the_private_call(F, monkeypatch):
+    """torch._C._cuda_getCurrentRawStream is a short cut: a torch without it serves the same stream by its public interface."""
+    import types
+    import torch
+    from paper_1801_00829_amd import api
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: types.SimpleNamespace(cuda_stream=0x1230))
+    monkeypatch.setattr(api, "_raw_stream", lambda device: 0x1000 + device)
+    assert api._stream(None).value == 0x1003
+    monkeypatch.setattr(api, "_raw_stream", None)
+    assert api._stream(None).value == 0x1230
+    assert api._stream(0x40).value == 0x40
