@@ -40,6 +40,9 @@ const char *kSrcRowMfma =
 const char *kSrcRowMfmaWave =
 #include "skel_row_mfma_wave.inc"
     ;
+const char *kSrcRowStored =
+#include "skel_row_stored.inc"
+    ;
 const char *kSrcRowMfmaPipe =
 #include "skel_row_mfma_pipe.inc"
     ;
@@ -556,6 +559,8 @@ int row_mfma_impl(const Program &prog, const std::string &pkey, const fuse_dense
              "\n#define FUSE_VSIDE " + std::to_string(vside) + "\n";
         s += side_tables(sides, nsides, prog.side_used);
         s += emit_row_body(prog);
+        if (csrx)
+            s += kSrcRowStored;
         s += pipe ? kSrcRowMfmaPipe : kSrcRowMfma;
         g_last_source = s;
         return s;

@@ -1424,6 +1424,44 @@ def test_row_csr_matrix_units_pipelined(n, k, rowptr64, monkeypatch):
     assert_close(got, unfused.row_csr(MLOGREG, x, hs, "col_t"), scale=2.0 * k * scale, what="csr pipelined")
 
 
+@pytest.mark.parametrize("n,k,pipe", [(128, 13, "3"), (300, 10, "3"), (640, 8, "3"), (1101, 5, "3"), (40, 14, "0"), (300, 5, "0")])
+def test_row_csr_matrix_units_multiply_stored_cells_only(n, k, pipe, monkeypatch):
+    """Values that are not finite, in V, in a k-vector side and in X, in both matrix-unit forms over CSR rows: infinite, NaN and
+    finite where the lane-group form is, and the finite values within 1e-10 of the largest one (of a column that a
+    value of V does not reach)."""
+    import paper_1801_00829_amd as F
+    monkeypatch.setenv("FUSE_MFMA_PIPE", pipe)
+    monkeypatch.setenv("FUSE_MFMA_CSR_DENSITY", "1")
+    m = 256 * 16 * 2 + 5
+    rng = np.random.default_rng(n + k)
+    mask = rng.uniform(size=(m, n)) < 0.03
+    mask[:, 5] = False
+    mask[[3, m - 1], 5] = True
+    rp, ci = np.concatenate([[0], np.cumsum(mask.sum(1))]), np.nonzero(mask)[1].astype(np.int32)
+    va = rng.uniform(0.1, 1.0, len(ci))
+    v, p = rng.normal(size=(n, k)), rng.uniform(size=(m, k))
+    for where in ("v", "p", "x", "nowhere"):
+        v2, p2, va2 = v.copy(), p.copy(), va.copy()
+        if where == "v":
+            v2[5, k - 1] = -np.inf
+        elif where == "p":
+            p2[100, 1], p2[m - 1, 0] = np.nan, np.inf
+        elif where == "x":
+            va2[len(va) // 2] = np.nan
+        xd, sides = dev_csr(rp, ci, va2, (m, n), False), [("rhs", to_dev(v2)), ("kvec", to_dev(p2))]
+        print("csr tiles", (n, k, pipe), where, flush=True)
+        got = host(F.fuse_row(MLOGREG, xd, sides, "col_t")).reshape(n, k)
+        assert F.last_kernel().startswith("fuse_row_mfma_") and ("_pipe_" in F.last_kernel()) == (pipe != "0")
+        monkeypatch.setenv("FUSE_MFMA_CSR_MIN_K", "0")
+        want = host(F.fuse_row(MLOGREG, xd, sides, "col_t")).reshape(n, k)
+        monkeypatch.delenv("FUSE_MFMA_CSR_MIN_K")
+        assert F.last_kernel().startswith("fuse_row_csr_")
+        finite = np.isfinite(want)
+        assert finite.all() == (where == "nowhere") and finite.any()
+        assert np.array_equal(finite, np.isfinite(got)) and np.array_equal(np.isnan(want), np.isnan(got))
+        assert np.abs(got - want)[finite].max() <= 1e-10 * np.abs(want[finite]).max()
+
+
 def test_row_matrix_rhs_strided_sides_and_limits(rhs_form):
     import paper_1801_00829_amd as F
     from oracle import plans

@@ -124,10 +124,10 @@ _Q = [("side", 1), ("main",), ("side", 0), ("matmult",), ("mul",)]
 MLOGREG = [("main",)] + _Q + [("side", 1)] + _Q + [("rowsum",), ("mul",), ("sub",), ("outerk",)]
 
 
-def _run_csr_pipe(F, folder, monkeypatch, mask, k, rp64=False, before=0, blocks=2, change=None, last_first=False):
-    """t(X) %*% f(X %*% V) over the cells that `mask` has, in CSR arrays that hold `before` cells in front of them.
-    Returns (result, X, V, P)."""
-    monkeypatch.setenv("FUSE_MFMA_PIPE", "3")
+def _run_csr_tiles(F, folder, monkeypatch, mask, k, pipe=True, rp64=False, before=0, blocks=2, change=None, last_first=False):
+    """t(X) %*% f(X %*% V) over the cells that `mask` has, in CSR arrays that hold `before` cells in front of them, in the
+    pipelined or the block form.  change(values): other operands.  Returns (result, oracle)."""
+    monkeypatch.setenv("FUSE_MFMA_PIPE", "3" if pipe else "0")
     monkeypatch.setenv("FUSE_MFMA_CSR_DENSITY", "1")
     m, n = mask.shape
     rng = np.random.default_rng(n + k)
@@ -139,7 +139,7 @@ def _run_csr_pipe(F, folder, monkeypatch, mask, k, rp64=False, before=0, blocks=
     F.cache_clear()
     F.prepare_row(MLOGREG, (m, n), [("rhs", (n, k)), ("kvec", (m, k))], "col_t", nnz=len(ci), rowptr64=rp64)
     name = F.last_kernel()
-    assert name.startswith("fuse_row_mfma_pipe_")
+    assert name.startswith("fuse_row_mfma_") and ("_pipe_" in name) == pipe
     kern = Kernels(F.last_source(), folder, [name])
     a = Args()
     side = [kern.copy(vals["v"]), kern.copy(vals["p"])]
@@ -150,14 +150,41 @@ def _run_csr_pipe(F, folder, monkeypatch, mask, k, rp64=False, before=0, blocks=
     a.m, a.n, a.ld, a.nnz = m, n, n, before + len(ci)
     for q, s in enumerate(side):
         a.side[q], a.side_ld[q] = _ptr(s), k
-    kern.run(name, a, blocks, (kern.define("FUSE_NWAVE") + 1) * 64, last_first)
-    return part.sum(0), ops.make_csr(rp - before, ci, vals["x"], (m, n)), vals["v"], vals["p"]
+    kern.run(name, a, blocks, (kern.define("FUSE_NWAVE") + int(pipe)) * 64, last_first)
+    with np.errstate(all="ignore"):
+        want = unfused.row_csr(MLOGREG, ops.make_csr(rp - before, ci, vals["x"], (m, n)), [("rhs", vals["v"]), ("kvec", vals["p"])], "col_t")
+        return part.sum(0), want.reshape(n, k)
 
 
 def test_csr_cells_at_the_end_of_32_bit_offsets(F, tmp_path, monkeypatch):
     """The last cells of a matrix with 2^31 - 1 stored ones and 32-bit row offsets (address space only)."""
     mask = np.random.default_rng(8).uniform(size=(41, 130)) < 0.2
-    got, x, v, p = _run_csr_pipe(F, tmp_path, monkeypatch, mask, 5, before=2 ** 31 - 1 - int(mask.sum()))
-    want = unfused.row_csr(MLOGREG, x, [("rhs", v), ("kvec", p)], "col_t").reshape(got.shape)
+    got, want = _run_csr_tiles(F, tmp_path, monkeypatch, mask, 5, before=2 ** 31 - 1 - int(mask.sum()))
     err = np.abs(got - want).max()
     assert err <= 1e-12 * np.abs(want).max()
+
+
+@pytest.mark.parametrize("where", ["v", "p", "x", "nowhere"])
+@pytest.mark.parametrize("pipe", [True, False])
+def test_csr_tiles_multiply_stored_cells_only(F, tmp_path, monkeypatch, pipe, where):
+    """An infinity in V reaches the rows that store its column, one in P or X the columns that its row stores; tiles that are
+    full, and one that is not."""
+    mask = np.random.default_rng(9).uniform(size=(53, 130)) < 0.15
+    mask[:, 7] = False
+    mask[[3, 50], 7] = True
+    mask[40] = False
+
+    def change(vals):
+        if where == "v":
+            vals["v"][7, 2] = np.inf
+        elif where == "p":
+            vals["p"][17, 1], vals["p"][52, 4], vals["p"][40, 0] = np.nan, np.inf, np.inf
+        elif where == "x":
+            vals["x"][100] = np.nan
+
+    got, want = _run_csr_tiles(F, tmp_path, monkeypatch, mask, 6, pipe, change=change)
+    finite = np.isfinite(want)
+    assert (where == "nowhere") == finite.all() and finite.any()
+    assert np.array_equal(finite, np.isfinite(got)) and np.array_equal(np.isnan(want), np.isnan(got))
+    err = np.abs(got - want)[finite].max()
+    assert err <= 1e-12 * np.abs(want[finite]).max()
