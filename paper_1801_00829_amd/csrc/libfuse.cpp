@@ -544,6 +544,9 @@ int row_mfma_impl(const Program &prog, const std::string &pkey, const fuse_dense
     const std::string key = std::string(pipe ? "rowmfmap|" : "rowmfma|") + pkey + "|" + side_key(sides, nsides) + "|v" + std::to_string(VEC) +
                             "n" + std::to_string(nct) + (pipe ? "w" + std::to_string(NPROD) + "r" + std::to_string(TR) + "l" + std::to_string(nld) : "w" + std::to_string(NWAVE)) + "nt" + std::to_string(env_int("FUSE_NT", 1)) +
                             (pipe ? "" : "m" + std::to_string(m4)) + (csrx ? "csr" + std::to_string(rp64) + "c" + std::to_string(cap) : "");
+    bool hides_nan = false;              // operators that can give a number for NaN
+    for (const Node &nd : prog.nodes)
+        hides_nan = hides_nan || nd.op == FUSE_OP_NEQ0 || nd.op == FUSE_OP_POW || (nd.op >= FUSE_OP_LT && nd.op <= FUSE_OP_NE);
     std::shared_ptr<Plan> plan;
     int rc = rt.plan(key, pipe ? "fuse_row_mfma_pipe" : "fuse_row_mfma", [&](const std::string &name) {
         std::string s = kSrcArgs;
@@ -560,7 +563,7 @@ int row_mfma_impl(const Program &prog, const std::string &pkey, const fuse_dense
         s += side_tables(sides, nsides, prog.side_used);
         s += emit_row_body(prog);
         if (csrx)
-            s += kSrcRowStored;
+            s += "#define FUSE_CHECK_V " + std::to_string(hides_nan) + "\n" + kSrcRowStored;
         s += pipe ? kSrcRowMfmaPipe : kSrcRowMfma;
         g_last_source = s;
         return s;

@@ -124,7 +124,7 @@ _Q = [("side", 1), ("main",), ("side", 0), ("matmult",), ("mul",)]
 MLOGREG = [("main",)] + _Q + [("side", 1)] + _Q + [("rowsum",), ("mul",), ("sub",), ("outerk",)]
 
 
-def _run_csr_tiles(F, folder, monkeypatch, mask, k, pipe=True, rp64=False, before=0, blocks=2, change=None, last_first=False):
+def _run_csr_tiles(F, folder, monkeypatch, mask, k, pipe=True, expr=MLOGREG, rp64=False, before=0, blocks=2, change=None, last_first=False):
     """t(X) %*% f(X %*% V) over the cells that `mask` has, in CSR arrays that hold `before` cells in front of them, in the
     pipelined or the block form.  change(values): other operands.  Returns (result, oracle)."""
     monkeypatch.setenv("FUSE_MFMA_PIPE", "3" if pipe else "0")
@@ -137,7 +137,7 @@ def _run_csr_tiles(F, folder, monkeypatch, mask, k, pipe=True, rp64=False, befor
     if change:
         change(vals)
     F.cache_clear()
-    F.prepare_row(MLOGREG, (m, n), [("rhs", (n, k)), ("kvec", (m, k))], "col_t", nnz=len(ci), rowptr64=rp64)
+    F.prepare_row(expr, (m, n), [("rhs", (n, k)), ("kvec", (m, k))], "col_t", nnz=len(ci), rowptr64=rp64)
     name = F.last_kernel()
     assert name.startswith("fuse_row_mfma_") and ("_pipe_" in name) == pipe
     kern = Kernels(F.last_source(), folder, [name])
@@ -152,7 +152,7 @@ def _run_csr_tiles(F, folder, monkeypatch, mask, k, pipe=True, rp64=False, befor
         a.side[q], a.side_ld[q] = _ptr(s), k
     kern.run(name, a, blocks, (kern.define("FUSE_NWAVE") + int(pipe)) * 64, last_first)
     with np.errstate(all="ignore"):
-        want = unfused.row_csr(MLOGREG, ops.make_csr(rp - before, ci, vals["x"], (m, n)), [("rhs", vals["v"]), ("kvec", vals["p"])], "col_t")
+        want = unfused.row_csr(expr, ops.make_csr(rp - before, ci, vals["x"], (m, n)), [("rhs", vals["v"]), ("kvec", vals["p"])], "col_t")
         return part.sum(0), want.reshape(n, k)
 
 
@@ -164,27 +164,28 @@ def test_csr_cells_at_the_end_of_32_bit_offsets(F, tmp_path, monkeypatch):
     assert err <= 1e-12 * np.abs(want).max()
 
 
-@pytest.mark.parametrize("where", ["v", "p", "x", "nowhere"])
+@pytest.mark.parametrize("where", ["v", "v, hidden", "p", "x", "nowhere"])
 @pytest.mark.parametrize("pipe", [True, False])
 def test_csr_tiles_multiply_stored_cells_only(F, tmp_path, monkeypatch, pipe, where):
     """An infinity in V reaches the rows that store its column, one in P or X the columns that its row stores; tiles that are
-    full, and one that is not."""
+    full, and one that is not.  "hidden": a body with a comparison, whose sums are finite whatever V holds."""
+    hidden = [("main",), ("main",), ("side", 0), ("matmult",), ("const", 0.0), ("gt",), ("side", 1), ("mul",), ("outerk",)]
     mask = np.random.default_rng(9).uniform(size=(53, 130)) < 0.15
     mask[:, 7] = False
     mask[[3, 50], 7] = True
     mask[40] = False
 
     def change(vals):
-        if where == "v":
+        if where.startswith("v"):
             vals["v"][7, 2] = np.inf
         elif where == "p":
             vals["p"][17, 1], vals["p"][52, 4], vals["p"][40, 0] = np.nan, np.inf, np.inf
         elif where == "x":
             vals["x"][100] = np.nan
 
-    got, want = _run_csr_tiles(F, tmp_path, monkeypatch, mask, 6, pipe, change=change)
+    got, want = _run_csr_tiles(F, tmp_path, monkeypatch, mask, 6, pipe, hidden if where == "v, hidden" else MLOGREG, change=change)
     finite = np.isfinite(want)
-    assert (where == "nowhere") == finite.all() and finite.any()
+    assert (where in ("nowhere", "v, hidden")) == finite.all() and finite.any()
     assert np.array_equal(finite, np.isfinite(got)) and np.array_equal(np.isnan(want), np.isnan(got))
     err = np.abs(got - want)[finite].max()
     assert err <= 1e-12 * np.abs(want[finite]).max()
