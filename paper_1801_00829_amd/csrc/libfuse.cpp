@@ -475,8 +475,8 @@ int row_mfma_impl(const Program &prog, const std::string &pkey, const fuse_dense
         const double avg = m > 0 ? (double)Xs->nnz / (double)m : 1.0;
         return (int)std::min<int64_t>(16, std::max<int64_t>(1, (int64_t)(avg * 1.34 / threads) + 1));
     };
-    // Pipelined form (FUSE_MFMA_PIPE: 0 never, 1 by the rules here and below, 2 wherever a tile fits, 3 for CSR input of any width too): 7 product waves (11 for CSR
-    // input, whose tiles travel in few registers) and one for the generated code, one block per CU; the most
+    // Pipelined form (FUSE_MFMA_PIPE: 0 never, 1 by the rules here and below, 2 wherever a dense tile fits and for CSR input of 256 to 560 columns
+    // and at most 12 classes, 3 for any CSR input whose tile fits as well): 7 product waves (11 for CSR input, whose tiles travel in few registers) and one for the generated code, one block per CU; the most
     // rows per tile of which four tiles fit in LDS, while V, the running sums and two travelling tiles leave a thread 60 of
     // its 256 (168) registers.  2.4 GB, logistic regression core, block form / pipelined: n = 128 k = 4 586 / 564, k = 16
     // 1285 / 1015 us; n = 256 460 / 466, 818 / 814; n = 500 540 / 438, 718 / 674; n = 784 494 / 436, 832 / 660; n = 1000
