@@ -1018,15 +1018,19 @@ int row_csr_impl(const Program &prog, const fuse_csr *X, const fuse_side *sides,
     // matrix units, 1.6e8 cells of dense tiles, n = 64 719 / - / 760 / 930, 112 451 / 452 / 524 / 660 / 655, 200 356 / 360 / 469 /
     // 538 / 543, 300 298 / 300 / 354 / 416 / 421, 500 248 / 252 / 304 / 367 / 373, 900 227 / 232 / 281 / 326 / 340.  Near the line, lane groups /
     // matrix units: 300 columns, 15 % stored, k = 5 226 / 474, 25 % 258 / 298; 500 columns k = 5 15 % 274 / 375, 25 % 320 / 248; 784
-    // columns k = 5 15 % 384 / 354; k = 10, 8 % stored: n = 300 491 / 514, 500 572 / 420, 784 669 / 403.
+    // columns k = 5 15 % 384 / 354; k = 10, 8 % stored: n = 300 491 / 514, 500 572 / 420, 784 669 / 403.  6e6 cells, even rows: 500 columns
+    // k = 7 14 % 63 / 74, k = 9 8 % 93 / 139, 11 % 116 / 107; 300 columns k = 9 14 % 82 / 101; 112 columns k = 13 8 % 295 / 369, 11 % 368 / 277,
+    // k = 16 5.5 % 745 / 525; 900 columns k = 13 3.5 % 361 / 311, k = 16 2 % 633 / 530.  Over 576 such calls (64 to 900
+    // columns, 5 to 16 classes, 1.4 to 60 % stored, 132 with log-normal rows) the choice takes 1.018 of the better form's time in the geometric mean; never more than
+    // 1.16 of the lane groups' below 15 % stored (112 columns, k = 13, 10 %), from there on up to twice with few columns (64 columns, k = 7, 20 % 71 / 134).
     {
         int vside = -1;
         const int min_k = env_int("FUSE_MFMA_CSR_MIN_K", 5);
         const double share = (m > 0 && n > 0) ? (double)X->nnz / ((double)m * (double)n) : 0.0;
         const int least = env_int("FUSE_MFMA_CSR_DENSITY", -1);
-        static const double lane_ps[FUSE_MAX_K + 1] = {1, 1, 2, 3, 5, 7, 7.7, 10, 18, 23, 30, 33, 36, 65, 85, 90, 100};
-        const double lanes = lane_ps[std::min(std::max(kd, 0), FUSE_MAX_K)] * (n < 400 ? 0.85 : 1.1);
-        const double tiles = (n < 100 ? 4.5 : n < 128 ? 2.9 : n < 256 ? 2.35 : n < 400 ? 1.87 : 1.5) * (kd <= 8 ? 1.0 : kd <= 12 ? 1.2 : 1.4);
+        static const double lane_ps[FUSE_MAX_K + 1] = {1, 1, 2, 3, 5, 7, 7.7, 9, 18, 17, 30, 33, 36, 65, 80, 93, 108};
+        const double lanes = lane_ps[std::min(std::max(kd, 0), FUSE_MAX_K)] * (kd >= 14 ? 1.0 : n < 400 ? 0.85 : 1.1);
+        const double tiles = (n < 100 ? 4.5 : n < 128 ? (kd <= 12 ? 2.9 : 3.57) : n < 256 ? 2.35 : n < 400 ? 1.87 : 1.5) * (kd <= 8 ? 1.0 : kd <= 12 ? 1.2 : 1.4);
         const bool pays = least >= 0 ? 100.0 * share >= (double)least : (share >= 0.15 && kd >= 7) || share * lanes >= tiles;
         const int64_t tile_bytes = (16 * ((n + 15) / 16 * 16 + 1) + (int64_t)(4 + 2 + std::max(nsides, 1)) * 272 + 128) * 8;
         if (ac == 3 && min_k > 0 && kd >= min_k && n >= 16 && tile_bytes <= 158 * 1024 && pays && mfma_pattern(prog, sides, nsides, vside))

@@ -680,3 +680,16 @@ def test_binding_finds_the_current_stream_without_the_private_call(F, monkeypatc
     monkeypatch.setattr(api, "_raw_stream", None)
     assert api._stream(None).value == 0x1230
     assert api._stream(0x40).value == 0x40
+
+
+@pytest.mark.parametrize("n,k,share,tiles", [(500, 9, 0.08, False), (500, 9, 0.12, True), (300, 9, 0.14, False), (500, 7, 0.14, False), (500, 7, 0.16, True),
+                                             (112, 13, 0.08, False), (112, 13, 0.11, True), (112, 16, 0.055, True), (900, 13, 0.035, True),
+                                             (500, 5, 0.15, False), (500, 5, 0.26, True), (500, 14, 0.02, False), (500, 16, 0.02, True)])
+def test_line_between_lane_groups_and_matrix_units(F, n, k, share, tiles):
+    """On either side of the line for the numbers of classes where an interpolated estimate took calls to the slower form (7, 9 and
+    13), and where it was right."""
+    m = int(6e6 / (n * share))
+    q = [("side", 1), ("main",), ("side", 0), ("matmult",), ("mul",)]
+    F.prepare_row([("main",)] + q + [("side", 1)] + q + [("rowsum",), ("mul",), ("sub",), ("outerk",)], (m, n),
+                  [("rhs", (n, k)), ("kvec", (m, k))], "col_t", nnz=int(m * n * share))
+    assert F.last_kernel().startswith("fuse_row_mfma_") == tiles
