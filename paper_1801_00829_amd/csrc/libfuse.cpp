@@ -484,8 +484,9 @@ int row_mfma_impl(const Program &prog, const std::string &pkey, const fuse_dense
     // k = 4 523 / 353, k = 16 1017 / 730.  CSR, 4e7 cells, a quarter stored, k = 5 / 10 / 16: n = 150 423 / 398, 683 / 498, 763 /
     // 582; 200 378 / 356, 565 / 469, 615 / 543; 300 442 / 298, 456 / 354, 473 / 421; 500 349 / 248, 355 / 304; 784 306 / 225,
     // 310 / 265, 322 / 319; 900 303 / 227, 325 / 281, 605 / 340; 1050 477 / 215, 453 / 262, 664 / 318; but 112 columns k = 10 524 /
-    // 556, 250 columns k = 5 / 8 321 / 336, 324 / 337, and where 13 classes and more halve the tile 500 columns 373 / 396, 650
-    // 331 / 362.  With log-normal rows 4e7 cells, 15 % stored, k = 10: n = 300 1281 / 566, 500 1064 / 481, 784 1097 / 462.
+    // 556, 241 to 256 columns k = 5 / 8 up to 321 / 336, 324 / 337, and where 13 classes and more halve the tile to 4 rows: 2e7 cells, k = 13
+    // / 16, n = 481 200 / 205, 199 / 205, 560 186 / 190, 187 / 194, 704 163 / 181, 181 / 185; 720 174 / 183, 241 / 188 (from here on the block
+    // form spills with 15 and 16 classes), 736 163 / 184, 188 / 189, 752 181 / 181 (k = 14 163 / 182), 180 / 185, 768 209 / 181, 222 / 188.  With log-normal rows 4e7 cells, 15 % stored, k = 10: n = 300 1281 / 566, 500 1064 / 481, 784 1097 / 462.
     int TR = 16;
     bool pipe = false;
     const int ns_ = std::max(nsides, 1), mp = (kd + 3) / 4, NPROD = Xs ? 11 : 7;
@@ -496,7 +497,7 @@ int row_mfma_impl(const Program &prog, const std::string &pkey, const fuse_dense
         const double avg = m > 0 ? (double)Xs->nnz / (double)m * tr : 1.0;
         return (int)std::min<double>(16.0, std::ceil((avg + 4.0 * std::sqrt(avg)) / (64.0 * NPROD)));
     };
-    const bool csr_pipe = Xs && Xs->nnz > 0 && (pipe_mode == 3 || (pipe_mode == 2 && n >= 256 && n <= 560 && kd <= 12) || (pipe_mode == 1 && n >= 128 && !(nct == 16 && kd <= 8) && !(kd > 12 && n > 480 && n <= 704)));
+    const bool csr_pipe = Xs && Xs->nnz > 0 && (pipe_mode == 3 || (pipe_mode == 2 && n >= 256 && n <= 560 && kd <= 12) || (pipe_mode == 1 && n >= 128 && !(nct == 16 && kd <= 8) && !(kd > 12 && n > 480 && n <= (kd <= 14 ? 752 : 704))));
     if (pipe_mode != 0 && (!Xs || csr_pipe)) {
         for (int tr = 16; tr >= 4 && !pipe; tr >>= 1) {
             const int64_t lds = (4 * tr * np_pipe + (int64_t)(2 * NPROD + 3 + ns_) * tr * (4 * mp + 1)) * 8;
@@ -517,8 +518,10 @@ int row_mfma_impl(const Program &prog, const std::string &pkey, const fuse_dense
     //    550 / 518, 113 582 / 623, 128 511 / 542 (k = 8 481 / 435, k = 16 800 / 676), 144 786 / 505;
     //  - few rows: three more steps than tiles.  GPU time of both launches, tiles of 8 and 16 rows, logistic regression core:
     //    1000 rows n = 256 k = 10 9.6 / 11.6, n = 500 14.2 / 16.6, 4000 rows 15.9 / 18.7 and 23.9 / 28.1, 8000 rows 25.1 /
-    //    20.6 and 27.5 / 30.3, 16000 rows n = 500 36.5 / 36.1; 5000 rows n = 120 11.9 / 13.4, n = 300 23.5 / 21.5; CSR, k = 5, 4000 rows n = 300 12.9 / 16.6, 8000 rows 21.1 /
-    //    19.0, n = 500 21.1 / 24.1.  (Three classes would take the vector form instead.)
+    //    20.6 and 27.5 / 30.3, 16000 rows n = 500 36.5 / 36.1; 5000 rows n = 120 11.9 / 13.4, n = 300 23.5 / 21.5; CSR, a quarter stored, calls one after the other: 4000 rows n = 150 k = 10 12.9 / 16.4, n = 300
+    //    k = 5 13.2 / 14.7, k = 10 16.6 / 19.5, 8000 rows 18.9 / 16.3, 21.3 / 16.2, 25.9 / 21.4; n = 500 k = 10 8000 rows 25.4 / 29.1, 16000 33.9 / 36.1, 32000
+    //    50.8 / 50.0.  CSR tiles of 4 rows are pipelined at any number of rows: n = 784 k = 10 1000 rows 21.4 / 20.1, 4000 31.9 / 31.2, n =
+    //    1000 26.3 / 22.8, 39.2 / 35.6; with 13 and more classes up to 900 columns and 4000 rows that is 0.75 to 1.19 of the block form.  (Three classes would take the vector form instead.)
     const int64_t cus = rt.num_cus();
     bool kvec = false;
     for (int q = 0; q < nsides; ++q)

@@ -693,3 +693,12 @@ def test_line_between_lane_groups_and_matrix_units(F, n, k, share, tiles):
     F.prepare_row([("main",)] + q + [("side", 1)] + q + [("rowsum",), ("mul",), ("sub",), ("outerk",)], (m, n),
                   [("rhs", (n, k)), ("kvec", (m, k))], "col_t", nnz=int(m * n * share))
     assert F.last_kernel().startswith("fuse_row_mfma_") == tiles
+
+
+@pytest.mark.parametrize("n,k,pipelined", [(704, 16, False), (720, 13, False), (752, 14, False), (720, 16, True), (753, 14, True), (784, 13, True), (480, 13, True)])
+def test_csr_tiles_of_four_rows_and_many_classes(F, n, k, pipelined):
+    """The block form where the pipelined one's eleven waves have places idle (13 and 14 classes up to 47 column tiles)."""
+    m, q = 100000, [("side", 1), ("main",), ("side", 0), ("matmult",), ("mul",)]
+    F.prepare_row([("main",)] + q + [("side", 1)] + q + [("rowsum",), ("mul",), ("sub",), ("outerk",)], (m, n),
+                  [("rhs", (n, k)), ("kvec", (m, k))], "col_t", nnz=m * n // 4)
+    assert F.last_kernel().startswith("fuse_row_mfma_") and F.last_kernel().startswith("fuse_row_mfma_pipe_") == pipelined
