@@ -23,9 +23,9 @@
  *     enqueues its kernel(s) on that stream and returns without synchronising;
  *     results are in `out` once the stream reaches that point.  The first call
  *     with a new descriptor compiles it (hipRTC, host-side, blocking).
- *   - libfuse owns a small per-(device, stream) workspace for block partials;
- *     two calls that overlap on the same stream handle from different host
- *     threads are not supported.  The workspace is allocated (hipMalloc) by the
+ *   - libfuse owns a small per-(device, stream) workspace for block partials; a
+ *     call holds it until its last kernel is enqueued, so calls of several host
+ *     threads on one stream handle take turns.  The workspace is allocated (hipMalloc) by the
  *     first call on a stream and grows to the largest request seen there; a call
  *     whose plan is cached and loaded and whose workspace is large enough only
  *     launches kernels (outputs are cleared by a fill kernel, arrival counters
@@ -269,15 +269,17 @@ int fuse_row(const fuse_expr *expr, const fuse_dense *Xd, const fuse_csr *Xs,
  *                  The library first transposes X into its workspace (a counting sort
  *                  by column, a few small kernels on the same stream; about 28 bytes
  *                  per stored cell) and then walks the columns like
- *                  RIGHT_MM walks the rows; the cells of a column are ordered by groups of rows,
- *                  inside a group as the sort's atomics left them, which is not fixed from run to run.
+ *                  RIGHT_MM walks the rows; the cells of a column are ordered by groups of rows where
+ *                  that walk takes column panels (below), and otherwise (and inside a group) as
+ *                  the sort's atomics left them, which is not fixed from run to run.
  *                  rows(X) < 2^27 (else a scatter with fp64 atomics on the output).
  * 1 <= r <= 1024.  When V is larger than a few MB, FULL and NONE first build a table of
  * per-row offsets into column panels in the library's workspace (one more kernel on
  * the same stream; (P+1) x rows(X) offsets, P <= 1024 panels) and rely on the
  * ascending column indices the CSR format prescribes for their speed (a row with
- * another order is taken as one panel).  RIGHT_MM and LEFT_MM do so too from rank 80 on
- * where the factor whose rows they add is larger than 12 MB. */
+ * another order is taken as one panel).  RIGHT_MM and LEFT_MM do so too at ranks 80 to 128
+ * where the factor whose rows they add is larger than 12 MB and X stores 1.5 million cells or
+ * more; a row (column) far longer than the others is then summed by a kernel of its own. */
 int fuse_outer(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, const fuse_dense *V,
                const fuse_side *sides, int nsides, int agg, double *out, void *stream);
 

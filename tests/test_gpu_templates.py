@@ -695,8 +695,9 @@ def _outer_mm_on_all_patterns(agg, rowptr64, left_mm_form):
 def test_outer_row_runs(r, rowptr64, monkeypatch):
     """The row-run form (a wave per cell, result rows beside U in LDS; forced here with tiny panels) at the edges of its parts:
     units of 64 cells and more, rows without cells, fewer rows than a block takes, one and two vectors per lane, a side
-    input per cell, values that are not finite, columns that do not ascend, and rows so long that the call falls
-    back to a row per wave.  Sums of at most 700 products of values below 1: 1e-12 of the largest is far above their rounding."""
+    input per cell, values that are not finite, columns that do not ascend (rows beyond what a wave takes are in
+    test_outer_row_runs_with_long_rows).  Sums of at most 700 products of values below 1: 1e-12 of the largest is far above their
+    rounding."""
     import torch
     import paper_1801_00829_amd as F
     monkeypatch.setenv("FUSE_OUTER_PANELS", "2")
@@ -710,7 +711,7 @@ def test_outer_row_runs(r, rowptr64, monkeypatch):
         side = rng.uniform(size=(m, 1))
         x = ops.make_csr(rp, ci, va, (m, n))
         sides = [("colvec", side)]
-        for limit in ("0", "1"):                     # "1": rows of more than the usual share of a wave go to the other kernel
+        for limit in ("0", "1"):                     # "1": the limit of a row's cells by rule (none of these reaches it)
             monkeypatch.setenv("FUSE_OUTER_RUNS", "2" if limit == "0" else "1")
             monkeypatch.setenv("FUSE_OUTER_RB", rb)
             for agg in ("right_mm", "left_mm") if limit == "0" else ("right_mm",):
@@ -720,7 +721,7 @@ def test_outer_row_runs(r, rowptr64, monkeypatch):
                 assert_close(got, unfused.outer(body, x, u, v, sides, agg), tol=1e-12, what="row runs %s" % agg)
                 if agg == "right_mm":
                     assert np.array_equal(got, host(F.fuse_outer(body, xd, to_dev(u), to_dev(v), dev_sides(sides), agg)))
-        for agg in ("full", "none"):                 # the sums and values of the same traversal
+        for agg in ("full", "none"):                 # sums and values keep the panel walk
             monkeypatch.setenv("FUSE_OUTER_RUNS", "2")
             got = host(F.fuse_outer(body, dev_csr(rp, ci, va, (m, n), rowptr64), to_dev(u), to_dev(v), dev_sides(sides), agg))
             assert_close(got, unfused.outer(body, x, u, v, sides, agg), tol=1e-12, what="row runs %s" % agg)
