@@ -33,7 +33,9 @@
  *     sequence of calls can be recorded into a HIP graph and replayed.  A call
  *     that still has to compile or to allocate while its stream is being
  *     captured fails (FUSE_ENOMEM / FUSE_ERUNTIME: the runtime refuses the
- *     allocation) and the capture is lost: warm up first.
+ *     allocation) and the capture is lost: warm up first. (Outer products that
+ *     need a table in the workspace take the form without one where there is
+ *     no room for it.)
  *   - Return value: FUSE_OK (0) or a negative fuse_status; on error nothing is
  *     enqueued and `fuse_last_error()` returns a thread-local message
  *     (including the hipRTC log for FUSE_ECOMPILE).

@@ -1442,7 +1442,7 @@ bool outer_pattern_grouped(const fuse_csr *X)
 // pattern: a prepared left_mm pattern of X (device), or nullptr
 int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, const fuse_dense *V,
                const fuse_side *sides, int nsides, int agg, double *out, void *stream_, bool launch,
-               const void *pattern = nullptr, bool with_pattern = false)
+               const void *pattern = nullptr, bool with_pattern = false, bool with_runs = true)
 {
     g_err.clear();
     Runtime &rt = Runtime::get();
@@ -1619,7 +1619,7 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
     // 50 / 71.  (Even rows; rows far longer than the others go to a kernel of their own, see A.row_limit.)
     const int runs_mode = env_int("FUSE_OUTER_RUNS", 1);
     int runs_rb = 0, runs_cap = 1;       // rows per block and round, and of how many the plan has room for (two plans, whatever the rows)
-    if (runs_mode != 0 && panel_mode != 0 && kmode == 2 && wrows > 0 && wcols > 0 && nvec <= 128 / VEC &&
+    if (with_runs && runs_mode != 0 && panel_mode != 0 && kmode == 2 && wrows > 0 && wcols > 0 && nvec <= 128 / VEC &&
         (wcols - 1) * G_->ld + r <= ((int64_t)1 << 28) - 2) {          // (31-bit offsets; lanes past a row's end load from byte 2^31 - 16 on)
         const int64_t row_bytes = nvec * VEC * 8;
         const int64_t cell_bytes = X->rowptr_is64 ? 8 : 4;
@@ -1690,6 +1690,22 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
                             std::to_string(kmode) + (transposed ? "T" : "") + (kmode == 2 && out_vec ? "o" : "") + "|v" + std::to_string(VEC) + "g" + std::to_string(G) + "e" +
                             std::to_string(EPL) + "u" + std::to_string(UNR) + "b" + std::to_string(KBLOCK) + "w" +
                             std::to_string(X->rowptr_is64 != 0);
+    // transposed matrix: scratch of the counting sort, column offsets, row and value of every cell
+    const size_t rpb = X->rowptr_is64 ? 8 : 4;
+    auto dbl = [](size_t bytes) { return (bytes + 15) / 16 * 2; };           // doubles, 16-byte granules
+    const size_t t_scratch = transposed && !with_pattern ? dbl(transpose_scratch_bytes(X->rows, X->cols, X->nnz, X->rowptr_is64)) : 0,
+                 t_ptr = dbl((size_t)(X->cols + 1) * rpb), t_row = dbl((size_t)X->nnz * 4),
+                 t_val = (size_t)X->nnz;
+    const size_t t_doubles = transposed && !with_pattern ? t_scratch + t_ptr + t_row + t_val : 0;
+    const int cus = rt.num_cus();
+    const size_t pp_doubles = panels ? ((size_t)(npanels + 1) * (size_t)wrows * rpb / 8 + 2) / 2 * 2 : 0;
+    // Row runs have a plan and a table in the workspace that the row mapping does without.  Where they cannot be had, because the call is being
+    // captured (no loading, no allocation) or memory has run out (below), the row mapping serves it.
+    const int64_t runs_gx = std::max<int64_t>(8, (int64_t)cus * std::max(1, env_int("FUSE_OUTER_PANEL_BLOCKS_PER_CU", 0)) / 8 * 8);
+    auto parts = [](int64_t blocks) { return ((size_t)blocks + 15) / 16 * 16; };
+    auto row_mapping = [&] { return outer_impl(expr, X, U, V, sides, nsides, agg, out, stream_, launch, pattern, with_pattern, false); };
+    if (runs_rb && launch && Runtime::captured(stream) && !rt.ready(key, stream, parts(runs_gx) + pp_doubles + t_doubles))
+        return row_mapping();
     std::shared_ptr<Plan> plan;
     rc = rt.plan(key, "fuse_outer", [&](const std::string &name) {
         std::string s = kSrcArgs;
@@ -1723,30 +1739,26 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
         return zero_fill(fn, out, mode == 0 ? 0 : out_count, stream);
     if (mode == 3 && !transposed && (rc = zero_fill(fn, out, out_count, stream)))
         return rc;
-    const int cus = rt.num_cus();
     const int NW = BLOCK / 64;
     int64_t gx = (wrows + NW - 1) / NW;
     gx = std::max<int64_t>(1, std::min<int64_t>(gx, (int64_t)cus * env_int("FUSE_OUTER_BLOCKS_PER_CU", 8)));
-    size_t pp_doubles = 0;
     if (panels) {
         // every block must be resident from the start: blocks that start late walk the panels out of
         // step with their XCD and evict the panel the others are using
         int bpc = env_int("FUSE_OUTER_PANEL_BLOCKS_PER_CU", 0);
         if (bpc <= 0)
-            bpc = stat_rcw || runs_rb ? 1 : rt.resident_blocks_per_cu(fn.main, KBLOCK);
-        gx = std::max<int64_t>(8, (int64_t)cus * bpc / 8 * 8);
-        pp_doubles = ((size_t)(npanels + 1) * (size_t)wrows * (X->rowptr_is64 ? 8 : 4) / 8 + 2) / 2 * 2;
+            bpc = stat_rcw ? 1 : rt.resident_blocks_per_cu(fn.main, KBLOCK);
+        gx = runs_rb ? runs_gx : std::max<int64_t>(8, (int64_t)cus * bpc / 8 * 8);
     }
-    const size_t part_doubles = ((size_t)gx + 15) / 16 * 16;
-    // transposed matrix: scratch of the counting sort, column offsets, row and value of every cell
-    const size_t rpb = X->rowptr_is64 ? 8 : 4;
-    auto dbl = [](size_t bytes) { return (bytes + 15) / 16 * 2; };           // doubles, 16-byte granules
-    const size_t t_scratch = transposed && !with_pattern ? dbl(transpose_scratch_bytes(X->rows, X->cols, X->nnz, X->rowptr_is64)) : 0,
-                 t_ptr = dbl((size_t)(X->cols + 1) * rpb), t_row = dbl((size_t)X->nnz * 4),
-                 t_val = (size_t)X->nnz;
-    const size_t t_doubles = transposed && !with_pattern ? t_scratch + t_ptr + t_row + t_val : 0;
+    const size_t part_doubles = parts(gx);
     Workspace ws;
-    if ((rc = rt.workspace(stream, part_doubles + pp_doubles + t_doubles, ws, g_err)))
+    rc = rt.workspace(stream, part_doubles + pp_doubles + t_doubles, ws, g_err);
+    if (rc == FUSE_ENOMEM && runs_rb) {
+        (void)hipGetLastError();
+        ws.in_use.unlock();
+        return row_mapping();
+    }
+    if (rc)
         return rc;
     fuse_kargs A;
     std::memset(&A, 0, sizeof A);

@@ -281,6 +281,36 @@ int Runtime::workspace(hipStream_t stream, size_t doubles, Workspace &ws, std::s
     return 0;
 }
 
+bool Runtime::ready(const std::string &key, hipStream_t stream, size_t doubles)
+{
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess)
+        return false;
+    std::shared_ptr<Plan> p;
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        auto w = ws_.find(std::make_pair(dev, stream));
+        auto it = plans_.find(key);
+        if (w == ws_.end() || !w->second.ticket || !w->second.partials || w->second.partial_doubles < doubles || it == plans_.end())
+            return false;
+        p = it->second;
+    }
+    Plan::Loaded fn;
+    return loaded(*p, fn);
+}
+
+bool Runtime::captured(hipStream_t stream)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (!stream)                          // (the null stream cannot be captured)
+        return false;
+    if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
 int Runtime::resident_blocks_per_cu(hipFunction_t f, int block)
 {
     std::lock_guard<std::mutex> lk(mu_);

@@ -85,6 +85,10 @@ public:
     // Workspace of (current device, stream) with room for `doubles` partials; waits for another thread's call that holds
     // it.  Not twice in one call.
     int workspace(hipStream_t stream, size_t doubles, Workspace &ws, std::string &err);
+    // Whether a call of this plan on `stream` would neither load code nor allocate (nothing is done here); and whether the
+    // stream is being captured, when it can do neither.
+    bool ready(const std::string &key, hipStream_t stream, size_t doubles);
+    static bool captured(hipStream_t stream);
     // Workgroups of `block` threads of kernel `f` that one compute unit holds at once (>= 1).
     int resident_blocks_per_cu(hipFunction_t f, int block);
     int launch(hipFunction_t f, unsigned gx, unsigned gy, unsigned block, hipStream_t stream,

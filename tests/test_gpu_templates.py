@@ -808,6 +808,43 @@ def test_outer_row_runs_over_a_prepared_pattern(rowptr64, monkeypatch):
     assert "fuse_outer_rows" in F.last_source()
 
 
+def test_outer_products_captured_with_and_without_their_table():
+    """A product of a size that takes row runs, captured on a stream that a small matrix has warmed up (row mapping: no room for the
+    panel table) and on one that holds it; replays on changed values against the eager call, eager work in between.
+    Sums of about 530 products of values below 1: 1e-12 of the largest is far above their rounding."""
+    import torch
+    import paper_1801_00829_amd as F
+    m, n, r = 3000, 20000, 100
+    rng = np.random.default_rng(5600)
+    rp, ci, va = W.csr_bernoulli(m, n, 0.0267, 80)
+    assert len(va) >= 1500000
+    x, u, v = dev_csr(rp, ci, va, (m, n), False), to_dev(rng.uniform(size=(m, r))), to_dev(rng.uniform(size=(n, r)))
+    rs, cs, vs = W.csr_bernoulli(50, 60, 0.2, 81)
+    small = dev_csr(rs, cs, vs, (50, 60), False)
+    body = [("main",), ("uvdot",), ("mul",), ("const", 0.125), ("add",)]
+    out, nan, kernels = torch.empty(m * r, dtype=torch.float64, device=u.device), float("nan"), set()
+    for warm in (small, x):
+        print("capture", "small" if warm is small else "large", flush=True)
+        s = torch.cuda.Stream()
+        s.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(s):
+            F.fuse_outer(body, warm, u[:50] if warm is small else u, v[:60] if warm is small else v, [], "right_mm")
+        s.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            F.fuse_outer(body, x, u, v, [], "right_mm", out=out)
+        kernels.add(F.last_kernel())
+        for rep in range(3):
+            x.vals.mul_(0.75)
+            out.fill_(nan)
+            g.replay()
+            torch.cuda.synchronize()
+            want = F.fuse_outer(body, x, u, v, [], "right_mm")
+            assert_close(host(out), host(want), tol=1e-12, what="replay %d" % rep)
+        assert_close(host(want), unfused.outer(body, ops.make_csr(rp, ci, host(x.vals), (m, n)), host(u), host(v), [], "right_mm"), tol=1e-12, what="captured")
+    assert len(kernels) == 2
+
+
 def test_outer_products_from_two_threads_on_one_stream(monkeypatch):
     """Two host threads, one stream, products that hand a panel table on between their kernels: every result is the one the
     thread gets alone, bit for bit."""

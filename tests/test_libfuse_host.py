@@ -702,3 +702,12 @@ def test_csr_tiles_of_four_rows_and_many_classes(F, n, k, pipelined):
     F.prepare_row([("main",)] + q + [("side", 1)] + q + [("rowsum",), ("mul",), ("sub",), ("outerk",)], (m, n),
                   [("rhs", (n, k)), ("kvec", (m, k))], "col_t", nnz=m * n // 4)
     assert F.last_kernel().startswith("fuse_row_mfma_") and F.last_kernel().startswith("fuse_row_mfma_pipe_") == pipelined
+
+
+def test_row_runs_leave_calls_without_room_to_the_row_mapping(F, tmp_path):
+    """No memory for the panel table, or a captured call on a stream that a smaller matrix has warmed up (row_runs_without_room.cpp)."""
+    exe = str(tmp_path / "row_runs_without_room")
+    subprocess.run(["/opt/rocm/bin/hipcc", "-std=c++17", "-O1", "--offload-arch=gfx950", "-rdynamic", os.path.join(ROOT, "tests", "row_runs_without_room.cpp"),
+                    "-L" + os.path.dirname(F.lib_path()), "-l:libfuse.so", "-o", exe, "-Wl,-rpath," + os.path.dirname(F.lib_path())], check=True)
+    r = subprocess.run([exe], timeout=120, capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
