@@ -1690,13 +1690,14 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
                             std::to_string(kmode) + (transposed ? "T" : "") + (kmode == 2 && out_vec ? "o" : "") + "|v" + std::to_string(VEC) + "g" + std::to_string(G) + "e" +
                             std::to_string(EPL) + "u" + std::to_string(UNR) + "b" + std::to_string(KBLOCK) + "w" +
                             std::to_string(X->rowptr_is64 != 0);
-    // transposed matrix: scratch of the counting sort, column offsets, row and value of every cell
+    // transposed matrix: scratch of the counting sort, column offsets, row and value of every cell (a matrix without any is not sorted)
+    const bool sorted = transposed && !with_pattern && X->rows > 0 && X->cols > 0 && X->nnz > 0;
     const size_t rpb = X->rowptr_is64 ? 8 : 4;
     auto dbl = [](size_t bytes) { return (bytes + 15) / 16 * 2; };           // doubles, 16-byte granules
-    const size_t t_scratch = transposed && !with_pattern ? dbl(transpose_scratch_bytes(X->rows, X->cols, X->nnz, X->rowptr_is64)) : 0,
+    const size_t t_scratch = sorted ? dbl(transpose_scratch_bytes(X->rows, X->cols, X->nnz, X->rowptr_is64)) : 0,
                  t_ptr = dbl((size_t)(X->cols + 1) * rpb), t_row = dbl((size_t)X->nnz * 4),
                  t_val = (size_t)X->nnz;
-    const size_t t_doubles = transposed && !with_pattern ? t_scratch + t_ptr + t_row + t_val : 0;
+    const size_t t_doubles = sorted ? t_scratch + t_ptr + t_row + t_val : 0;
     const int cus = rt.num_cus();
     const size_t pp_doubles = panels ? ((size_t)(npanels + 1) * (size_t)wrows * rpb / 8 + 2) / 2 * 2 : 0;
     // Row runs have a plan and a table in the workspace that the row mapping does without.  Where they cannot be had, because the call is being

@@ -711,3 +711,11 @@ def test_row_runs_leave_calls_without_room_to_the_row_mapping(F, tmp_path):
                     "-L" + os.path.dirname(F.lib_path()), "-l:libfuse.so", "-o", exe, "-Wl,-rpath," + os.path.dirname(F.lib_path())], check=True)
     r = subprocess.run([exe], timeout=120, capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+@pytest.mark.parametrize("shape,nnz", [((0, 40), 0), ((40, 0), 0), ((0, 0), 0), ((40, 30), 0)])
+@pytest.mark.parametrize("agg", ["right_mm", "left_mm", "full", "none"])
+def test_outer_over_empty_matrices_sizes_no_sort(F, shape, nnz, agg):
+    """The scratch of the transposition is asked for where there are cells to sort: it counts rows per block, and there are none."""
+    F.prepare_outer([("main",), ("uvdot",), ("mul",)], shape, 100, nnz, [], agg)
+    assert F.last_kernel().startswith("fuse_outer_")
