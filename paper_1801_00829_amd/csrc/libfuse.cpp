@@ -1620,7 +1620,8 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
     const int runs_mode = env_int("FUSE_OUTER_RUNS", 1);
     int runs_rb = 0, runs_cap = 1;       // rows per block and round, and of how many the plan has room for (two plans, whatever the rows)
     if (with_runs && runs_mode != 0 && panel_mode != 0 && kmode == 2 && wrows > 0 && wcols > 0 && nvec <= 128 / VEC &&
-        (wcols - 1) * G_->ld + r <= ((int64_t)1 << 28) - 2) {          // (31-bit offsets; lanes past a row's end load from byte 2^31 - 16 on)
+        (wcols - 1) * G_->ld + r <= ((int64_t)1 << 28) - 2 &&          // (31-bit offsets; lanes past a row's end load from byte 2^31 - 16 on)
+        (runs_mode == 2 || panel_mode == 2 || (r >= 80 && outer_panels_pay(X->nnz, wcols, nvec * VEC * 8)))) {
         const int64_t row_bytes = nvec * VEC * 8;
         const int64_t cell_bytes = X->rowptr_is64 ? 8 : 4;
         // (beside the rows: the books of four panels)
@@ -1639,15 +1640,14 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
         const int64_t pkb = env_int("FUSE_OUTER_RPANEL_KB", 0);
         w = pkb > 0 ? (double)(pkb * 1024) / (double)row_bytes : std::min(w, 8.0e6 / (double)row_bytes);
         const int64_t grain = !transposed ? 1 : with_pattern && !outer_pattern_grouped(X) ? 0 : transpose_row_grain(X->rows, X->cols, X->nnz);
-        const bool pays = outer_panels_pay(X->nnz, wcols, row_bytes);
-        if (grain > 0 && (runs_mode == 2 || panel_mode == 2 || pays)) {
+        if (grain > 0) {
             int64_t W = std::max<int64_t>(1, std::min<int64_t>((int64_t)w, panel_mode == 2 ? (wcols + 7) / 8 : wcols));
             W = std::max<int64_t>(grain, (W + grain / 2) / grain * grain);
             W = std::max<int64_t>(W, (wcols + 1023) / 1024);
             W = (W + grain - 1) / grain * grain;
             const int64_t P = (wcols + W - 1) / W;
             if (P >= 2 && (P + 1) * wrows * cell_bytes <= ((int64_t)1 << 30) &&
-                (runs_mode == 2 || panel_mode == 2 || (per_row / (double)P >= 3.0 && r >= 80))) {
+                (runs_mode == 2 || panel_mode == 2 || per_row / (double)P >= 3.0)) {
                 runs_rb = (int)rb;
                 runs_cap = (int)(rb <= 64 ? std::min<int64_t>(64, cap) : cap);
                 npanels = (int)P;
@@ -1702,7 +1702,7 @@ int outer_impl(const fuse_expr *expr, const fuse_csr *X, const fuse_dense *U, co
     const size_t pp_doubles = panels ? ((size_t)(npanels + 1) * (size_t)wrows * rpb / 8 + 2) / 2 * 2 : 0;
     // Row runs have a plan and a table in the workspace that the row mapping does without.  Where they cannot be had, because the call is being
     // captured (no loading, no allocation) or memory has run out (below), the row mapping serves it.
-    const int64_t runs_gx = std::max<int64_t>(8, (int64_t)cus * std::max(1, env_int("FUSE_OUTER_PANEL_BLOCKS_PER_CU", 0)) / 8 * 8);
+    const int64_t runs_gx = !runs_rb ? 0 : std::max<int64_t>(8, (int64_t)cus * std::max(1, env_int("FUSE_OUTER_PANEL_BLOCKS_PER_CU", 0)) / 8 * 8);
     auto parts = [](int64_t blocks) { return ((size_t)blocks + 15) / 16 * 16; };
     auto row_mapping = [&] { return outer_impl(expr, X, U, V, sides, nsides, agg, out, stream_, launch, pattern, with_pattern, false); };
     if (runs_rb && launch && Runtime::captured(stream) && !rt.ready(key, stream, parts(runs_gx) + pp_doubles + t_doubles))
